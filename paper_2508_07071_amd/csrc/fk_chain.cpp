@@ -1,6 +1,8 @@
 // fk_chain.cpp -- chain rewriting done once per plan (no HIP).
 #include "fk_chain.hpp"
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <utility>
@@ -148,6 +150,151 @@ void fk::merge_repeats(std::vector<OpRec> &ops)
         k = j;
     }
     ops.swap(out);
+}
+
+// ----------------------------------------------------------- lowering --
+
+static bool channels_equal(const fk::OpRec &r, int C)
+{
+    for (int c = 1; c < C; ++c)
+        if (std::memcmp(&r.a[c], &r.a[0], 4) != 0 || std::memcmp(&r.b[c], &r.b[0], 4) != 0)
+            return false;
+    return true;
+}
+
+template <typename V>
+static void put(std::vector<uint8_t> &pool, V x)
+{
+    const size_t n = pool.size();
+    pool.resize(n + sizeof x);
+    std::memcpy(pool.data() + n, &x, sizeof x);
+}
+
+static void align16(std::vector<uint8_t> &pool) { pool.resize((pool.size() + 15) & ~(size_t)15); }
+
+static void mul_add(const fk::OpRec &r, int c, double &m, double &a)
+{
+    m = r.code == fk::OPC_ADD ? 1.0 : r.a[c];
+    a = r.code == fk::OPC_ADD ? r.a[c] : r.code == fk::OPC_MUL ? -0.0 : r.b[c];
+}
+
+template <typename V>
+static void put_fma(std::vector<uint8_t> &pool, const fk::OpRec &r, bool shared)
+{
+    double m[4], a[4];
+    for (int c = 0; c < 4; ++c)
+        mul_add(r, c, m[c], a[c]);
+    if (shared) {
+        put(pool, (V)m[0]);
+        put(pool, (V)a[0]);
+        return;
+    }
+    for (int c = 0; c < 4; ++c)
+        put(pool, (V)m[c]);
+    for (int c = 0; c < 4; ++c)
+        put(pool, (V)a[c]);
+}
+
+static void put_div(std::vector<uint8_t> &pool, const fk::OpRec &r, int C, bool f64)
+{
+    int e = 1;  // the smallest biased exponent of the fast form
+    for (int c = 0; c < C; ++c) {
+        if (f64) {
+            const double d = r.a[c];
+            uint64_t u;
+            std::memcpy(&u, &d, 8);
+            e = std::max(e, (int)((u >> 52) & 2047) - 899);
+        } else {
+            uint32_t u;
+            std::memcpy(&u, &r.a[c], 4);
+            e = std::max(e, (int)((u >> 23) & 255) - 125);
+        }
+    }
+    if (f64) {
+        fk::DivRec64 q;
+        std::memset(&q, 0, sizeof q);
+        for (int c = 0; c < 4; ++c) {
+            const double d = c < C ? r.a[c] : 1.0, zh = 1.0 / d;
+            q.d[c] = d;
+            q.zh[c] = zh;
+            // the rest of the reciprocal: 1 - d zh is exact in one fma
+            q.zl[c] = std::isfinite(zh) && std::isfinite(d) ? std::fma(-d, zh, 1.0) / d : 0.0;
+        }
+        q.thr = ((uint32_t)e << 21) - 1u;
+        put(pool, q);
+    } else {
+        fk::DivRec32 q;
+        std::memset(&q, 0, sizeof q);
+        for (int c = 0; c < 4; ++c) {
+            q.d[c] = c < C ? r.a[c] : 1.0f;
+            q.y[c] = 1.0 / (double)q.d[c];
+        }
+        q.thr = ((uint32_t)e << 24) - 1u;
+        put(pool, q);
+    }
+}
+
+void fk::lower_ops(const std::vector<OpRec> &ops, int C, bool f64, std::vector<uint8_t> &prog)
+{
+    const size_t n = ops.size();
+    std::vector<char> edge(n + 1, 0);  // a loop body starts here: no stretch crosses it
+    for (size_t k = 0; k < n; ++k)
+        if (ops[k].code == OPC_LOOP && ops[k].span > 1)
+            edge[k - (size_t)ops[k].span] = 1;
+    std::vector<OpSeg> segs;
+    std::vector<size_t> first(n + 1, 0);  // a record's segment
+    std::vector<uint8_t> pool;
+    auto reps_of = [&](size_t k) {
+        return k + 1 < n && ops[k + 1].code == OPC_LOOP && ops[k + 1].span == 1 ? ops[k + 1].count : 1;
+    };
+    size_t k = 0;
+    while (k < n) {
+        first[k] = segs.size();
+        const OpRec &r = ops[k];
+        if (r.code == OPC_LOOP) {
+            if (r.span > 1) {  // a one-record loop is its record's `reps`
+                const size_t body = segs.size() - first[k - (size_t)r.span];
+                segs.push_back(OpSeg{SEG_LOOP, (int32_t)body, 0, r.count});
+            }
+            ++k;
+            continue;
+        }
+        align16(pool);
+        OpSeg s = {SEG_DIV, 1, (uint32_t)pool.size(), reps_of(k)};
+        if (r.code == OPC_DIV) {
+            put_div(pool, r, C, f64);
+            ++k;
+        } else if (s.reps > 1) {
+            s.kind = SEG_FMAR;
+            f64 ? put_fma<double>(pool, r, false) : put_fma<float>(pool, r, false);
+            ++k;
+        } else {
+            // the stretch of multiply-adds from here: up to a division, a
+            // loop, the start of a loop body or a repeated record
+            size_t j = k;
+            bool shared = true;
+            while (j < n && ops[j].code != OPC_LOOP && ops[j].code != OPC_DIV && reps_of(j) == 1 &&
+                   (j == k || !edge[j])) {
+                shared = shared && channels_equal(ops[j], C);
+                first[j] = segs.size();
+                ++j;
+            }
+            s.kind = shared ? SEG_FMA1 : SEG_FMAC;
+            s.n = (int32_t)(j - k);
+            for (; k < j; ++k)
+                f64 ? put_fma<double>(pool, ops[k], shared) : put_fma<float>(pool, ops[k], shared);
+        }
+        segs.push_back(s);
+    }
+    segs.push_back(OpSeg{SEG_END, 0, 0, 1});
+    align16(pool);
+    const uint32_t base = (uint32_t)(segs.size() * sizeof(OpSeg));
+    for (OpSeg &s : segs)
+        s.off += base;
+    // 128 bytes past the last constant: the kernels fetch one group ahead
+    prog.assign(base + pool.size() + 128, 0);
+    std::memcpy(prog.data(), segs.data(), base);
+    std::copy(pool.begin(), pool.end(), prog.begin() + base);
 }
 
 // Runs of each record code when the list executes, loops unrolled

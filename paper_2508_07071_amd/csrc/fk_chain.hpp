@@ -20,6 +20,10 @@ void normalise_chain(const fk_chain_desc *ch, bool strict, std::vector<OpRec> &o
 // normalise_chain.
 void merge_repeats(std::vector<OpRec> &ops);
 void executed_counts(const std::vector<OpRec> &ops, double cnt[4]);
+// The normalised list as the kernels run it: OpSeg records, then their
+// constants (fp64 constants when f64).  The buffer is padded so that a
+// kernel may fetch one group of constants past any segment's last.
+void lower_ops(const std::vector<OpRec> &ops, int channels, bool f64, std::vector<uint8_t> &prog);
 // FAM_NORMALIZE / FAM_MULADD / FAM_MULADD_LOOP with their constants (and
 // op count, or the loop's count of pairs) when the chain is one of the
 // compile-time chains, else FAM_RUNTIME.

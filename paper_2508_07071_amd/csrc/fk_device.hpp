@@ -848,15 +848,128 @@ struct LoopMulAddCompute {
 };
 
 // ------------------------------------------------------ run-time ops --
-// The op list is uniform across the grid: each op is one scalar branch and
-// its constants come through the scalar cache, then applied to all values
-// the thread holds (a register group of its units).  A LOOP record over one record
-// makes that record run `count` times in a register loop; a longer LOOP
-// jumps back over its body until the body has run `count` times (bodies
-// hold no loops, so one counter serves every loop of the list).
+// The op list is uniform across the grid: OpSeg records and their constants
+// come through the scalar cache, and each record is applied, in place, to
+// all values the thread holds (a register group of its units).
+//
+// Bound by VALU issue on lists of more than a few records.  The list used
+// to be one record per op with a branch on its code; the values reached each
+// branch's merge through register copies (three per value and record, and
+// twice the registers), and a division was the general 12-instruction
+// sequence.  Now a stretch of multiply-adds is one loop that fetches its
+// constants one group ahead, and a division by a constant takes 4 to 6
+// instructions (DivRec32, DivRec64; 12.6 cycles a wave for the fp32 form
+// alone against 48 for the general one).  Measured: a 4K fp32 frame through
+// 64 mul/add in fp64 203 -> 68 us, 48 u8 crops to 256 x 256 through 29 ops
+// into planar fp16 46.3 -> 32.5 us, the same bits.
 // fused multiply-add in the running value's precision
 __device__ __forceinline__ float fma_v(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_v(double a, double b, double c) { return fma(a, b, c); }
+
+template <typename V, int K, int P, int C>
+__device__ __forceinline__ void fma_shared(V (&v)[K][P][C], V m, V a)
+{
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                v[j][i][c] = fma_v(v[j][i][c], m, a);
+}
+
+// k: V m[4], a[4]
+template <typename V, int K, int P, int C>
+__device__ __forceinline__ void fma_channels(V (&v)[K][P][C], const V (&k)[8])
+{
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                v[j][i][c] = fma_v(v[j][i][c], k[c], k[4 + c]);
+}
+
+template <typename V>
+__device__ __forceinline__ void load8(const FK_CONST V *q, V (&k)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        k[i] = q[i];
+}
+
+// One division of every value by its channel's constant: the fast form
+// where every lane's dividends allow it, else the general division.  A
+// branch of the wave, so that both forms work in place.
+template <int K, int P, int C>
+__device__ __forceinline__ void div_values(float (&v)[K][P][C], const FK_CONST DivRec32 *q)
+{
+    uint32_t lo = 0xffffffffu;  // zero wraps to the largest value
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const uint32_t u = (__builtin_bit_cast(uint32_t, v[j][i][c]) << 1) - 1u;
+                lo = u < lo ? u : lo;
+            }
+    if (__builtin_amdgcn_ballot_w64(lo < q->thr) == 0) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    v[j][i][c] = (float)((double)v[j][i][c] * q->y[c]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    v[j][i][c] = v[j][i][c] / q->d[c];
+    }
+}
+
+template <int K, int P, int C>
+__device__ __forceinline__ void div_values(double (&v)[K][P][C], const FK_CONST DivRec64 *q)
+{
+    uint32_t lo = 0xffffffffu;
+    bool sub = false;  // a subnormal may have a zero high word, as zero has
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const uint32_t u =
+                    ((uint32_t)(__builtin_bit_cast(uint64_t, v[j][i][c]) >> 32) << 1) - 1u;
+                lo = u < lo ? u : lo;
+                sub |= __builtin_amdgcn_class(v[j][i][c], 0x90);
+            }
+    if (__builtin_amdgcn_ballot_w64(lo < q->thr || sub) == 0) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const double x = v[j][i][c];
+                    v[j][i][c] = __builtin_amdgcn_div_fixup(fma(x, q->zh[c], x * q->zl[c]), q->d[c], x);
+                }
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    v[j][i][c] = v[j][i][c] / q->d[c];
+    }
+}
 
 // The run-time op list on fp32 values, or on fp64 values for a chain with
 // an fp64 write (the op's fp32 constants taken exactly).
@@ -864,68 +977,82 @@ struct RuntimeCompute {
     template <int K, int C, typename V, int P>
     __device__ __forceinline__ static void apply(const KArgs &a, V (&v)[K][P][C])
     {
-        const FK_CONST OpRec *ops = cptr(a.ops);
+        using Div = typename std::conditional<sizeof(V) == 8, DivRec64, DivRec32>::type;
+        const FK_CONST OpSeg *segs = cptr(a.ops);
+        const FK_CONST uint8_t *base = (const FK_CONST uint8_t *)segs;
         int runs = 1;  // runs of the current loop body so far
-        for (int o = 0; o < a.n_ops; ++o) {
-            const int code = ops[o].code;
-            if (code == OPC_LOOP) {
-                if (ops[o].span == 1)
-                    continue;  // already run by its one-record body, below
-                if (runs < ops[o].count) {
+        // One `if` per kind, each on a bit of its own: with else branches the
+        // values would live twice, before and after the merge.
+#pragma unroll 1
+        for (int i = 0;; ++i) {
+            const int kind = segs[i].kind;
+            if (kind & SEG_END)
+                break;
+            const FK_CONST V *q = (const FK_CONST V *)(base + segs[i].off);
+            if (kind & SEG_FMA1) {
+                // four records' constants per fetch, the next four in flight
+                int n = segs[i].n;
+                V k[8];
+                load8(q, k);
+#pragma unroll 1
+                while (n >= 4) {
+                    V nx[8];
+                    q += 8;
+                    load8(q, nx);
+                    fma_shared(v, k[0], k[1]);
+                    fma_shared(v, k[2], k[3]);
+                    fma_shared(v, k[4], k[5]);
+                    fma_shared(v, k[6], k[7]);
+                    n -= 4;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        k[t] = nx[t];
+                }
+                if (n >= 1)
+                    fma_shared(v, k[0], k[1]);
+                if (n >= 2)
+                    fma_shared(v, k[2], k[3]);
+                if (n >= 3)
+                    fma_shared(v, k[4], k[5]);
+            }
+            if (kind & SEG_DIV) {
+                int reps = segs[i].reps;
+#pragma unroll 1
+                do
+                    div_values(v, (const FK_CONST Div *)q);
+                while (--reps > 0);
+            }
+            if (kind & SEG_FMAC) {
+                int n = segs[i].n;
+                V k[8];
+                load8(q, k);
+#pragma unroll 1
+                do {
+                    V nx[8];
+                    q += 8;
+                    load8(q, nx);
+                    fma_channels(v, k);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        k[t] = nx[t];
+                } while (--n > 0);
+            }
+            if (kind & SEG_FMAR) {
+                int reps = segs[i].reps;
+                V k[8];
+                load8(q, k);
+#pragma unroll 1
+                do
+                    fma_channels(v, k);
+                while (--reps > 0);
+            }
+            if (kind & SEG_LOOP) {
+                if (runs < segs[i].reps) {
                     ++runs;
-                    o -= ops[o].span + 1;  // the loop's ++o lands on the body's first record
+                    i -= segs[i].n + 1;  // the loop's ++i lands on the body's first segment
                 } else {
                     runs = 1;
                 }
-                continue;
-            }
-            // a record followed by a one-record LOOP runs `count` times here,
-            // in a register loop with its constants loaded once
-            int reps = 1;
-            if (o + 1 < a.n_ops && ops[o + 1].code == OPC_LOOP && ops[o + 1].span == 1)
-                reps = ops[o + 1].count;
-            V ka[C], kb[C];
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                ka[c] = (V)ops[o].a[c];
-                kb[c] = (V)ops[o].b[c];
-            }
-            if (code == OPC_FMA) {
-                for (int r = 0; r < reps; ++r)
-#pragma unroll
-                    for (int j = 0; j < K; ++j)
-#pragma unroll
-                        for (int i = 0; i < P; ++i)
-#pragma unroll
-                            for (int c = 0; c < C; ++c)
-                                v[j][i][c] = fma_v(v[j][i][c], ka[c], kb[c]);
-            } else if (code == OPC_MUL) {
-                for (int r = 0; r < reps; ++r)
-#pragma unroll
-                    for (int j = 0; j < K; ++j)
-#pragma unroll
-                        for (int i = 0; i < P; ++i)
-#pragma unroll
-                            for (int c = 0; c < C; ++c)
-                                v[j][i][c] = v[j][i][c] * ka[c];
-            } else if (code == OPC_ADD) {
-                for (int r = 0; r < reps; ++r)
-#pragma unroll
-                    for (int j = 0; j < K; ++j)
-#pragma unroll
-                        for (int i = 0; i < P; ++i)
-#pragma unroll
-                            for (int c = 0; c < C; ++c)
-                                v[j][i][c] = v[j][i][c] + ka[c];
-            } else {
-                for (int r = 0; r < reps; ++r)
-#pragma unroll
-                    for (int j = 0; j < K; ++j)
-#pragma unroll
-                        for (int i = 0; i < P; ++i)
-#pragma unroll
-                            for (int c = 0; c < C; ++c)
-                                v[j][i][c] = v[j][i][c] / ka[c];
             }
         }
     }
@@ -1174,6 +1301,24 @@ __device__ __forceinline__ void tile_item(const KArgs &a, const FK_CONST KArgs *
     ubase = (tile - first_tile) * tile_units;
 }
 
+// A move of every value cuts the tile loose from the register tuples of the
+// wide loads before the op list or the wide stores after it, whose order the
+// allocator otherwise keeps by copies at every segment of the list.
+template <int G, int C>
+__device__ __forceinline__ void own_registers(float (&v)[G][kUnitPx][C])
+{
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                float t;
+                asm("v_mov_b32 %0, %1" : "=v"(t) : "v"(v[j][i][c]));
+                v[j][i][c] = t;
+            }
+}
+
 // Units of a thread's K that k_transform holds in registers at once.  A
 // block of up to 1024 threads leaves each lane 128 VGPRs; past that the
 // compiler spills the register tile to scratch, and such launches ran 4-5x
@@ -1181,10 +1326,9 @@ __device__ __forceinline__ void tile_item(const KArgs &a, const FK_CONST KArgs *
 // K = 8 against 24 us at K <= 4).  So the K units go through in groups of
 // G, each loaded, computed and stored before the next: G = K where the
 // whole tile fits, else the largest group that compiles without scratch
-// (from the kernels' scratch sizes): 4 units of 3 channels, 2 of 4, and
-// half that for the run-time op list into planar fp32, whose per-channel
-// 16-byte stores gather each value anew (once more halved for fp32 plain
-// reads); 2 for the NV12 resize read.
+// (from the kernels' scratch sizes): 4 units of 3 channels, 2 of 4; 2 for
+// the run-time op list into planar fp32 (91 registers where 4 would leave
+// four waves a SIMD), for the NV12 resize read and for the nearest read.
 template <class Read, class Compute, class Write, int C, int K>
 constexpr int unit_group()
 {
@@ -1193,10 +1337,8 @@ constexpr int unit_group()
     int g = C == 1 ? 8 : C == 3 ? 4 : 2;
     if (rt && planar32 && C == 3)
         g = 2;
-    if (rt && planar32 && Read::kind == RD_PLAIN && Read::elem_size == 4)
-        g /= 2;
-    if (Read::kind == RD_NV12_RESIZE && g > 2)
-        g = 2;  // four converted taps per pixel
+    if ((Read::kind == RD_NV12_RESIZE || (rt && Read::kind == RD_CROP_NEAREST)) && g > 2)
+        g = 2;  // four converted taps per pixel; 64-bit source indices
     return K < g ? K : g;
 }
 
@@ -1279,7 +1421,14 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
                 }
             }
 
+            constexpr bool rt = std::is_same<Compute, RuntimeCompute>::value;
+            if constexpr (rt && Read::kind == RD_PLAIN && Read::elem_size == 4)
+                own_registers(v);
+
             Compute::template apply<G, C>(a, v);
+
+            if constexpr (rt && Write::layout == LY_PLANAR && Write::dtype == DT_F32)
+                own_registers(v);
 
 #pragma unroll
             for (int j = 0; j < G; ++j) {

@@ -389,10 +389,11 @@ extern "C" fk_status fk_plan_create(const fk_chain_desc *chain, int32_t max_batc
                               hipMemcpyHostToDevice);
         }
         if (e == hipSuccess) {
-            e = hipMalloc(&p->d_ops, std::max<size_t>(p->ops.size(), 1) * sizeof(OpRec));
-            if (e == hipSuccess && !p->ops.empty())
-                e = hipMemcpy(p->d_ops, p->ops.data(), p->ops.size() * sizeof(OpRec),
-                              hipMemcpyHostToDevice);
+            std::vector<uint8_t> prog;
+            lower_ops(p->ops, chain->read.channels, f64, prog);
+            e = hipMalloc(&p->d_ops, prog.size());
+            if (e == hipSuccess)
+                e = hipMemcpy(p->d_ops, prog.data(), prog.size(), hipMemcpyHostToDevice);
         }
         if (e == hipSuccess && stats) {
             // partials for every slot of a full batch
@@ -563,9 +564,8 @@ KArgs fk::make_args(const fk_plan *p, void *d_table)
     a.hdr = (const RunHeader *)d_table;
     a.items = (const ItemRec *)((const RunHeader *)d_table + 1);
     a.tile_begin = (const uint32_t *)(a.items + p->max_batch);
-    a.ops = (const OpRec *)p->d_ops;
+    a.ops = (const OpSeg *)p->d_ops;
     a.consts = (const float *)p->d_consts;
-    a.n_ops = (int32_t)p->ops.size();
     a.swap = runs_op_list(p) ? p->swap : 0;
     a.strict = p->opts.strict_fp;
     a.loop_count = p->family == FAM_MULADD_LOOP ? p->static_n : 0;

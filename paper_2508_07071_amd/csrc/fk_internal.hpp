@@ -45,6 +45,52 @@ struct OpRec {          // 48 bytes
     float b[4];         // FMA addend per channel
 };
 
+// The op list as the kernels run it (lower_ops): OpSeg records up to a
+// SEG_END, then a pool of constants in the running value's type V (fp32, or
+// fp64 for a chain with an fp64 write).  MUL, ADD and FMA records all become
+// multiply-adds, so a stretch of them is one loop with no branch on the op:
+// x * k is fma(x, k, -0.0) and x + k is fma(x, 1, k), each with the same one
+// rounding (and the same signed zero) as the op itself.
+enum : int32_t {
+    SEG_FMA1 = 1,  // n records, constants shared by the channels: V m, a
+    SEG_FMAC = 2,  // n records, constants per channel: V m[4], a[4]
+    SEG_FMAR = 4,  // one record per channel (as SEG_FMAC), run `reps` times
+    SEG_DIV = 8,   // one division (DivRec32 / DivRec64), run `reps` times
+    SEG_LOOP = 16, // the n segments before it run `reps` times in all
+    SEG_END = 32,  // after the last segment
+};
+struct OpSeg {          // 16 bytes
+    int32_t kind;
+    int32_t n;
+    uint32_t off;       // the segment's constants, bytes from the list's start
+    int32_t reps;
+};
+static_assert(sizeof(OpSeg) == 16, "OpSeg layout");
+
+// Division by a constant d, correctly rounded without the general division
+// sequence, where every dividend of the group is zero, infinite, NaN or
+// has a biased exponent of at least E (thr = (E << exponent shift) - 1 in
+// the high word shifted left by one); other groups take the general division.
+//  fp32: (float)((double)x * y) with y = RN64(1 / d).  The product is within
+//  2^-51.9 of x / d, and a quotient of two 24-bit numbers that is not
+//  subnormal lies at least 2^-49 from every rounding boundary, so it rounds
+//  as x / d does; E keeps the quotient normal.
+//  fp64: fma(x, zh, x * zl) with zh + zl = 1 / d to 2^-106.  d has 24 bits,
+//  so the quotient lies at least 2^-78 from every rounding boundary; E keeps
+//  it above 2^-900.  v_div_fixup sets the zeros, infinities and NaN.
+struct DivRec32 {       // 64 bytes
+    double y[4];
+    float d[4];
+    uint32_t thr;
+    uint32_t pad[3];
+};
+struct DivRec64 {       // 112 bytes
+    double zh[4], zl[4], d[4];
+    uint32_t thr;
+    uint32_t pad[3];
+};
+static_assert(sizeof(DivRec32) == 64 && sizeof(DivRec64) == 112, "division record layout");
+
 // Item flags.
 enum : int32_t {
     IF_SRC_VEC = 1,     // source rows 4-byte aligned: unit loads as dwords
@@ -115,9 +161,9 @@ struct KArgs {
     const RunHeader *hdr;
     const ItemRec *items;
     const uint32_t *tile_begin;
-    const OpRec *ops;      // run-time tier op list (device), n_ops entries
+    const OpSeg *ops;      // run-time tier op list (device), lowered, up to its SEG_END
     const float *consts;   // compile-time tier constants (device)
-    int32_t n_ops;
+    int32_t pad0;
     int32_t swap;          // net BGR<->RGB swap applied at the read
     int32_t strict;        // compile-time tier: 1 = no contraction
     int32_t loop_count;    // compile-time loop chain: pairs to run
