@@ -4,7 +4,31 @@
 
 #include <stdint.h>
 
+#include "../../include/fk.h"
+
 namespace fk {
+
+constexpr int kMlpIn = FK_MODEL_FEATURES, kMlpOut = FK_MODEL_OUTPUTS;
+static_assert(kMlpIn == 32 && kMlpOut <= 32, "the fused passes' input and output tiles");
+// Networks of at most this many hidden units take the fused passes: a layer
+// is then one 16-column tile per wave of a block and its weights fit a
+// wave's registers; wider ones take one product per launch.
+constexpr int kMlpMaxH = 128;
+
+// Parameters (or gradients) of the layers in -> H -> H -> H -> out, weights
+// row-major [outputs][inputs].
+struct MlpNet {
+    const float *w[4], *b[4];
+    int H;
+};
+struct MlpGrad {
+    float *w[4], *b[4];
+};
+// x (n x in) -> hidden layers h[0..2] (n x H each) and y (n x out)
+hipError_t mlp_forward(const MlpNet &net, const float *x, float *const h[3], float *y, int n, hipStream_t s);
+// every gradient from dy (n x out); d1, d2: n x H each, written
+hipError_t mlp_backward(const MlpNet &net, const float *x, const float *const h[3], const float *dy, float *d1,
+                        float *d2, const MlpGrad &out, int n, hipStream_t s);
 
 enum : int { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_RELU_MASK = 3 };
 

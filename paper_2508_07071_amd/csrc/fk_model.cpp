@@ -50,7 +50,7 @@ struct fk_model {
     // workspace for up to ws_rows rows
     int ws_rows = 0;
     float *d_act[kLayers + 1] = {};
-    float *d_delta[2] = {};
+    float *d_delta[3] = {};  // the loss gradient, and two propagated ones
     float *d_target = nullptr;
     float *d_loss = nullptr;  // one slot per mini-batch of an epoch
     int loss_slots = 0;
@@ -156,7 +156,7 @@ fk_status ensure_ws(fk_model *m, int rows)
     hipError_t e = hipSuccess;
     for (int l = 0; l <= kLayers && e == hipSuccess; ++l)
         e = hipMalloc(&m->d_act[l], sizeof(float) * (size_t)rows * m->dims[l]);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i)
+    for (int i = 0; i < 3 && e == hipSuccess; ++i)
         e = hipMalloc(&m->d_delta[i], sizeof(float) * (size_t)rows * widest);
     if (e == hipSuccess)
         e = hipMalloc(&m->d_target, sizeof(float) * (size_t)rows * O);
@@ -191,10 +191,23 @@ void standardize(const fk_model *m, const float *in, int n, std::vector<float> &
             out[(size_t)r * F + c] = (in[(size_t)r * F + c] - m->mean[c]) / m->stdv[c];
 }
 
+MlpNet net_of(const fk_model *m)
+{
+    MlpNet net = {};
+    for (int l = 0; l < kLayers; ++l) {
+        net.w[l] = m->d_params + m->w_off[l];
+        net.b[l] = m->d_params + m->b_off[l];
+    }
+    net.H = m->H;
+    return net;
+}
+
 // x (rows x F) -> hidden layers hid[0..2] (rows x H each) -> y (rows x O)
 hipError_t forward_p(const fk_model *m, const float *x, float *const hid[kLayers - 1], float *y,
                      int rows, hipStream_t st)
 {
+    if (m->H <= kMlpMaxH)
+        return mlp_forward(net_of(m), x, hid, y, rows, st);
     hipError_t e = hipSuccess;
     const float *in = x;
     for (int l = 0; l < kLayers && e == hipSuccess; ++l) {
@@ -215,6 +228,14 @@ hipError_t forward_p(const fk_model *m, const float *x, float *const hid[kLayers
 hipError_t backward_p(const fk_model *m, const float *x, float *const hid[kLayers - 1],
                       const float *dy, float *const tmp[2], float *grad, int rows, hipStream_t st)
 {
+    if (m->H <= kMlpMaxH) {
+        MlpGrad out = {};
+        for (int l = 0; l < kLayers; ++l) {
+            out.w[l] = grad + m->w_off[l];
+            out.b[l] = grad + m->b_off[l];
+        }
+        return mlp_backward(net_of(m), x, hid, dy, tmp[0], tmp[1], out, rows, st);
+    }
     hipError_t e = hipSuccess;
     const float *cur = dy;
     int nb = 0;
@@ -248,7 +269,7 @@ hipError_t forward(fk_model *m, int rows, hipStream_t st)
 hipError_t backward(fk_model *m, int rows, hipStream_t st)
 {
     float *hid[kLayers - 1] = {m->d_act[1], m->d_act[2], m->d_act[3]};
-    float *tmp[2] = {m->d_delta[1], m->d_delta[0]};
+    float *tmp[2] = {m->d_delta[1], m->d_delta[2]};
     return backward_p(m, m->d_act[0], hid, m->d_delta[0], tmp, m->d_grads, rows, st);
 }
 
