@@ -60,6 +60,11 @@ typedef FK_GLOBAL uint8_t *gdst_t;
 typedef float fx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t ux4 __attribute__((ext_vector_type(4)));
 typedef uint32_t ux2 __attribute__((ext_vector_type(2)));
+// The same at element alignment: global memory takes wide accesses at any
+// address, so a whole unit moves as dwords wherever its row starts.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef fx4 fx4_any __attribute__((aligned(4)));
+typedef ux2 ux2_any __attribute__((aligned(2)));
 
 template <int DT>
 struct DSize;
@@ -140,8 +145,12 @@ __device__ __forceinline__ void store_elem<DT_F16>(gdst_t p, float v)
 
 // ---------------------------------------------------------- read ops --
 
-// Plain read: the ROI 1:1.  Loads one unit (4 pixels) of output row oy
-// starting at column ox0; returns the number of valid pixels.
+// Plain read: the ROI 1:1.  Loads one unit (4 pixels, n valid) of output row
+// oy starting at column ox0; a whole unit as dwords at whatever alignment its
+// row has (element loads, one per value, took 4 to 12 times the instructions
+// on frames of odd width: 9 fp16 frames of 1501 x 1103 x 3 through 37 ops into
+// planar fp32 took 298 us that way, and take 67 us now; the bytes take 51 at
+// a large copy's rate).
 template <int DT, int C>
 struct ReadPlain {
     static constexpr int kind = RD_PLAIN;
@@ -153,10 +162,10 @@ struct ReadPlain {
         constexpr int ES = DSize<DT>::v;
         gsrc_t row = (gsrc_t)it.src + (int64_t)(it.y + oy) * it.pitch +
                      (int64_t)(it.x + ox0) * (C * ES);
-        if (n == kUnitPx && (it.flags & IF_SRC_VEC)) {
+        if (n == kUnitPx) {
             constexpr int NW = kUnitPx * C * ES / 4;
             uint32_t w[NW];
-            const FK_GLOBAL uint32_t *p = (const FK_GLOBAL uint32_t *)row;
+            const FK_GLOBAL u32_any *p = (const FK_GLOBAL u32_any *)row;
 #pragma unroll
             for (int i = 0; i < NW; ++i)
                 w[i] = p[i];
@@ -1073,18 +1082,19 @@ struct WritePlanar {
         const int64_t plane = (int64_t)it.ow * it.oh;
         const int64_t p0 = (int64_t)oy * it.ow + ox0;
         gdst_t dst = (gdst_t)it.dst;
-        if (n == kUnitPx && (it.flags & IF_DST_VEC)) {
+        if (n == kUnitPx) {
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 gdst_t q = dst + (c * plane + p0) * ES;
                 if constexpr (DT == DT_F32) {
-                    store_nt(q, fx4{r[0][c], r[1][c], r[2][c], r[3][c]});
+                    __builtin_nontemporal_store(fx4_any{r[0][c], r[1][c], r[2][c], r[3][c]},
+                                                (FK_GLOBAL fx4_any *)q);
                 } else {
                     uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)r[0][c]) |
                                   ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)r[1][c]) << 16);
                     uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)r[2][c]) |
                                   ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)r[3][c]) << 16);
-                    store_nt(q, ux2{lo, hi});
+                    __builtin_nontemporal_store(ux2_any{lo, hi}, (FK_GLOBAL ux2_any *)q);
                 }
             }
         } else {
@@ -1366,15 +1376,16 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
         ItemRec it;
         uint32_t ubase;
         tile_item<Read, C>(a, ka, compact, tb, items, n_items, tile, total, tile_units, it, ubase);
-        const uint32_t upr = (uint32_t)(it.ow + kUnitPx - 1) / kUnitPx;
-        const uint32_t units = upr * (uint32_t)it.oh;
-        const RowDiv rowdiv(upr);
-
         // a plain read of whole frame rows stored back to back (and its
-        // output) is one row of ow * oh pixels: no row division
+        // output) is one row of ow * oh pixels: no row division, and one
+        // partial unit in all instead of one a row
         bool contig = false;
         if constexpr (Read::kind == RD_PLAIN)
             contig = it.flags & IF_CONTIG;
+        const int row_px = contig ? it.ow * it.oh : it.ow;
+        const uint32_t upr = (uint32_t)(row_px + kUnitPx - 1) / kUnitPx;
+        const uint32_t units = contig ? upr : upr * (uint32_t)it.oh;
+        const RowDiv rowdiv(upr);
         constexpr int G = unit_group<Read, Compute, Write, C, K>();
 #pragma unroll 1
         for (int g0 = 0; g0 < K; g0 += G) {
@@ -1387,14 +1398,13 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
                     if (contig) {
                         oy[j] = 0;
                         ox0[j] = (int)(u * kUnitPx);
-                        nv[j] = kUnitPx;
                     } else {
                         const uint32_t row = rowdiv(u);
                         oy[j] = (int)row;
                         ox0[j] = (int)(u - row * upr) * kUnitPx;
-                        const int left = it.ow - ox0[j];
-                        nv[j] = left < kUnitPx ? left : kUnitPx;
                     }
+                    const int left = row_px - ox0[j];
+                    nv[j] = left < kUnitPx ? left : kUnitPx;
                     Read::load(it, oy[j], ox0[j], nv[j], v[j]);
                 } else {
                     oy[j] = 0;

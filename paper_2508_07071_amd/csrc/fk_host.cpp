@@ -496,6 +496,9 @@ uint32_t fk::build_items(const fk_plan *p, const fk_item *items, int32_t n,
         stats ? std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)kStatSlots, p->st_capacity / batch,
                                                           persistent_grid(p, cfg) / batch}))
               : ~0ull;
+    // k_transform takes a contiguous item as one row; the other kernels of
+    // plain reads count the units of every row
+    const bool one_row_units = !stats && !per_pixel(p) && p->family != FAM_F64;
     uint64_t tiles = 0;
     for (int32_t b = 0; b < n; ++b) {
         const fk_item &it = items[b];
@@ -526,17 +529,19 @@ uint32_t fk::build_items(const fk_plan *p, const fk_item *items, int32_t n,
         if ((uintptr_t)it.src.ptr % 4 == 0 && it.src.pitch_bytes % 4 == 0 &&
             ((int64_t)it.x * C * es_in) % 4 == 0)
             flags |= IF_SRC_VEC;
-        if (r.ow % kUnitPx == 0 && (uintptr_t)it.dst % 16 == 0)
-            flags |= IF_DST_VEC;
         if (small_frame(it.src))
             flags |= IF_SMALL_FRAME;
         if (p->chain.read.kind == FK_READ_PLAIN && it.x == 0 && it.w == it.src.width &&
-            it.src.pitch_bytes == (int64_t)it.src.width * C * es_in && r.ow % kUnitPx == 0 &&
+            it.src.pitch_bytes == (int64_t)it.src.width * C * es_in &&
             (int64_t)r.ow * r.oh < ((int64_t)1 << 31))
             flags |= IF_CONTIG;
+        const bool one_row = one_row_units && (flags & IF_CONTIG);
+        if ((one_row || r.ow % kUnitPx == 0) && (uintptr_t)it.dst % 16 == 0)
+            flags |= IF_DST_VEC;
         r.flags = flags;
         tb[b] = (uint32_t)tiles;
-        const uint64_t units = (uint64_t)upr * (uint64_t)r.oh;
+        const uint64_t units = one_row ? ((uint64_t)r.ow * (uint64_t)r.oh + kUnitPx - 1) / kUnitPx
+                                       : (uint64_t)upr * (uint64_t)r.oh;
         tiles += std::min<uint64_t>((units + tile_units - 1) / tile_units, slot_cap);
     }
     tb[n] = (uint32_t)tiles;

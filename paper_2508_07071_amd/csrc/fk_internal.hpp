@@ -94,10 +94,11 @@ static_assert(sizeof(DivRec32) == 64 && sizeof(DivRec64) == 112, "division recor
 // Item flags.
 enum : int32_t {
     IF_SRC_VEC = 1,     // source rows 4-byte aligned: unit loads as dwords
-    IF_DST_VEC = 2,     // output rows hold whole units and are 16/8-byte aligned
-    IF_CONTIG = 4,      // plain read of whole frame rows stored back to back, whole
-                        // units per row, under 2^31 pixels: unit u starts u * 4
-                        // pixels after row y
+    IF_DST_VEC = 2,     // output 16-byte aligned, its rows (IF_CONTIG: its pixels, but
+                        // for the last ones) whole units
+    IF_CONTIG = 4,      // plain read of whole frame rows stored back to back, under
+                        // 2^31 pixels: one row of ow * oh pixels, unit u starting
+                        // u * 4 pixels after row y
     IF_SMALL_FRAME = 8, // frame below 4 GiB, rows below 16 MiB: 32-bit row offsets
 };
 
