@@ -195,43 +195,39 @@ static void put_fma(std::vector<uint8_t> &pool, const fk::OpRec &r, bool shared)
         put(pool, (V)a[c]);
 }
 
-static void put_div(std::vector<uint8_t> &pool, const fk::OpRec &r, int C, bool f64)
+fk::DivRec32 fk::div_record(const float d[4], int C)
 {
+    DivRec32 q;
+    std::memset(&q, 0, sizeof q);
     int e = 1;  // the smallest biased exponent of the fast form
-    for (int c = 0; c < C; ++c) {
-        if (f64) {
-            const double d = r.a[c];
-            uint64_t u;
-            std::memcpy(&u, &d, 8);
-            e = std::max(e, (int)((u >> 52) & 2047) - 899);
-        } else {
-            uint32_t u;
-            std::memcpy(&u, &r.a[c], 4);
-            e = std::max(e, (int)((u >> 23) & 255) - 125);
-        }
+    for (int c = 0; c < 4; ++c) {
+        q.d[c] = c < C ? d[c] : 1.0f;
+        q.y[c] = 1.0 / (double)q.d[c];
+        uint32_t u;
+        std::memcpy(&u, &q.d[c], 4);
+        e = std::max(e, c < C ? (int)((u >> 23) & 255) - 125 : 1);
     }
-    if (f64) {
-        fk::DivRec64 q;
-        std::memset(&q, 0, sizeof q);
-        for (int c = 0; c < 4; ++c) {
-            const double d = c < C ? r.a[c] : 1.0, zh = 1.0 / d;
-            q.d[c] = d;
-            q.zh[c] = zh;
-            // the rest of the reciprocal: 1 - d zh is exact in one fma
-            q.zl[c] = std::isfinite(zh) && std::isfinite(d) ? std::fma(-d, zh, 1.0) / d : 0.0;
-        }
-        q.thr = ((uint32_t)e << 21) - 1u;
-        put(pool, q);
-    } else {
-        fk::DivRec32 q;
-        std::memset(&q, 0, sizeof q);
-        for (int c = 0; c < 4; ++c) {
-            q.d[c] = c < C ? r.a[c] : 1.0f;
-            q.y[c] = 1.0 / (double)q.d[c];
-        }
-        q.thr = ((uint32_t)e << 24) - 1u;
-        put(pool, q);
+    q.thr = ((uint32_t)e << 24) - 1u;
+    return q;
+}
+
+static fk::DivRec64 div_record64(const float d[4], int C)
+{
+    fk::DivRec64 q;
+    std::memset(&q, 0, sizeof q);
+    int e = 1;
+    for (int c = 0; c < 4; ++c) {
+        const double x = c < C ? d[c] : 1.0, zh = 1.0 / x;
+        q.d[c] = x;
+        q.zh[c] = zh;
+        // the rest of the reciprocal: 1 - d zh is exact in one fma
+        q.zl[c] = std::isfinite(zh) && std::isfinite(x) ? std::fma(-x, zh, 1.0) / x : 0.0;
+        uint64_t u;
+        std::memcpy(&u, &x, 8);
+        e = std::max(e, c < C ? (int)((u >> 52) & 2047) - 899 : 1);
     }
+    q.thr = ((uint32_t)e << 21) - 1u;
+    return q;
 }
 
 void fk::lower_ops(const std::vector<OpRec> &ops, int C, bool f64, std::vector<uint8_t> &prog)
@@ -262,7 +258,7 @@ void fk::lower_ops(const std::vector<OpRec> &ops, int C, bool f64, std::vector<u
         align16(pool);
         OpSeg s = {SEG_DIV, 1, (uint32_t)pool.size(), reps_of(k)};
         if (r.code == OPC_DIV) {
-            put_div(pool, r, C, f64);
+            f64 ? put(pool, div_record64(r.a, C)) : put(pool, div_record(r.a, C));
             ++k;
         } else if (s.reps > 1) {
             s.kind = SEG_FMAR;

@@ -24,6 +24,8 @@ void executed_counts(const std::vector<OpRec> &ops, double cnt[4]);
 // constants (fp64 constants when f64).  The buffer is padded so that a
 // kernel may fetch one group of constants past any segment's last.
 void lower_ops(const std::vector<OpRec> &ops, int channels, bool f64, std::vector<uint8_t> &prog);
+// The record of a division of fp32 values by d[c], c < channels.
+DivRec32 div_record(const float d[4], int channels);
 // FAM_NORMALIZE / FAM_MULADD / FAM_MULADD_LOOP with their constants (and
 // op count, or the loop's count of pairs) when the chain is one of the
 // compile-time chains, else FAM_RUNTIME.

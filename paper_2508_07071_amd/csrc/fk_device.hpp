@@ -184,14 +184,28 @@ struct ReadPlain {
     }
 };
 
+// A unit of a gathering read: its pixels' columns, with those past the row's
+// end moved onto its last column (read, not stored): no branch per pixel, so
+// that the loads of all four are in flight together.
+template <class Read, int C>
+__device__ __forceinline__ void load_unit_pxs(const ItemRec &it, int oy, int ox0, float (&r)[kUnitPx][C])
+{
+    int ys[kUnitPx], xs[kUnitPx];
+#pragma unroll
+    for (int i = 0; i < kUnitPx; ++i) {
+        ys[i] = oy;
+        xs[i] = ox0 + i < it.ow ? ox0 + i : it.ow - 1;
+    }
+    Read::load_pxs(it, Read::px_prep(it), ys, xs, r);
+}
+
 // Half-pixel source coordinate of output index o, clamped below at 0, with
 // its two taps (clamped to the ROI) and the fractional weight.
 __device__ __forceinline__ void bilinear_coord(int o, float scale, int in_size, int &i0, int &i1,
                                                float &a)
 {
-    float s = fmaf((float)o + 0.5f, scale, -0.5f);
-    s = s < 0.0f ? 0.0f : s;
-    int lo = (int)floorf(s);
+    const float s = fmaxf(fmaf((float)o + 0.5f, scale, -0.5f), 0.0f);
+    int lo = (int)s;  // floor: s >= 0
     lo = lo > in_size - 1 ? in_size - 1 : lo;
     i0 = lo;
     i1 = lo + 1 < in_size ? lo + 1 : in_size - 1;
@@ -226,11 +240,10 @@ struct ReadCropResize {
         }
     }
 
-    // bytes [0, 2C) of the tap pair starting at absolute address `addr`
-    __device__ __forceinline__ static void window(uint64_t addr, uint32_t (&d)[2])
+    // bytes [0, 2C) of the tap pair at p's dword-aligned window, sh = the
+    // pair's offset in it (0..3)
+    __device__ __forceinline__ static void window(const FK_GLOBAL uint32_t *p, uint32_t sh, uint32_t (&d)[2])
     {
-        const FK_GLOBAL uint32_t *p = (const FK_GLOBAL uint32_t *)(addr & ~(uint64_t)3);
-        const uint32_t sh = (uint32_t)(addr & 3);
         if constexpr (WB == 8) {
             const uint32_t w0 = p[0], w1 = p[1];
             d[0] = __builtin_amdgcn_alignbyte(w1, w0, sh);
@@ -240,6 +253,16 @@ struct ReadCropResize {
             d[0] = __builtin_amdgcn_alignbyte(w1, w0, sh);
             d[1] = __builtin_amdgcn_alignbyte(w2, w1, sh);
         }
+    }
+    __device__ __forceinline__ static void window_at(uint64_t addr, uint32_t (&d)[2])
+    {
+        window((const FK_GLOBAL uint32_t *)(addr & ~(uint64_t)3), (uint32_t)(addr & 3), d);
+    }
+    // the same at a 32-bit offset from the (dword-aligned, uniform) frame
+    // base: the load takes the base as a scalar, no 64-bit address per lane
+    __device__ __forceinline__ static void window_off(gsrc_t base, uint32_t off, uint32_t (&d)[2])
+    {
+        window((const FK_GLOBAL uint32_t *)(base + (uint64_t)(off & ~3u)), off & 3u, d);
     }
 
     __device__ __forceinline__ static float byte_at(const uint32_t (&d)[2], int k)
@@ -258,8 +281,8 @@ struct ReadCropResize {
         bilinear_coord(ox, it.sx, it.w, x0, x1, ax);
         if (DT == DT_U8 && win) {
             uint32_t t[2], b[2];
-            window((uint64_t)(uintptr_t)(r0 + x0 * C), t);
-            window((uint64_t)(uintptr_t)(r1 + x0 * C), b);
+            window_at((uint64_t)(uintptr_t)(r0 + x0 * C), t);
+            window_at((uint64_t)(uintptr_t)(r1 + x0 * C), b);
             lerp_windows(t, b, x1 == x0, ax, ay, r);
             return;
         }
@@ -280,26 +303,45 @@ struct ReadCropResize {
     }
 
     // the pixel from the byte windows of its top and bottom tap rows (tap
-    // pair at bytes [0, 2C), or one pixel at [0, C) when the right tap is
-    // clamped onto the left one)
+    // pair at bytes [0, 2C)).  A right tap clamped onto the left one gives
+    // the left tap's value: weight 0 on whatever byte follows does too, and
+    // keeps the byte positions fixed.
     __device__ __forceinline__ static void lerp_windows(const uint32_t (&t)[2], const uint32_t (&b)[2],
                                                         bool clamped, float ax, float ay, float (&r)[C])
     {
-        const int o1 = clamped ? 0 : C;
-        float p00[C], p01[C], p10[C], p11[C];
+        ax = clamped ? 0.0f : ax;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            p00[c] = byte_at(t, c);
-            p01[c] = byte_at(t, o1 + c);
-            p10[c] = byte_at(b, c);
-            p11[c] = byte_at(b, o1 + c);
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const float top = fmaf(ax, p01[c] - p00[c], p00[c]);
-            const float bot = fmaf(ax, p11[c] - p10[c], p10[c]);
+            const float p00 = byte_at(t, c), p01 = byte_at(t, C + c);
+            const float p10 = byte_at(b, c), p11 = byte_at(b, C + c);
+            const float top = fmaf(ax, p01 - p00, p00);
+            const float bot = fmaf(ax, p11 - p10, p10);
             r[c] = fmaf(ay, bot - top, top);
         }
+    }
+
+    // output pixel (ox, oy) of an item that takes windows, in a frame of
+    // 32-bit offsets (IF_SMALL_FRAME); o0, o1: its source rows' offsets
+    __device__ __forceinline__ static void rows_off(const ItemRec &it, int oy, uint32_t &o0, uint32_t &o1,
+                                                    float &ay)
+    {
+        int y0, y1;
+        bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
+        const uint32_t col = (uint32_t)it.x * C;
+        o0 = __umul24((uint32_t)(it.y + y0), (uint32_t)it.pitch) + col;
+        o1 = __umul24((uint32_t)(it.y + y1), (uint32_t)it.pitch) + col;
+    }
+    __device__ __forceinline__ static void pixel_off(const ItemRec &it, uint32_t o0, uint32_t o1, float ay, int ox,
+                                                     float (&r)[C])
+    {
+        int x0, x1;
+        float ax;
+        bilinear_coord(ox, it.sx, it.w, x0, x1, ax);
+        const uint32_t x = __umul24((uint32_t)x0, (uint32_t)C);
+        uint32_t t[2], b[2];
+        window_off((gsrc_t)it.src, o0 + x, t);
+        window_off((gsrc_t)it.src, o1 + x, b);
+        lerp_windows(t, b, x1 == x0, ax, ay, r);
     }
 
     // source rows of output row oy, and the vertical weight.  A frame
@@ -321,34 +363,50 @@ struct ReadCropResize {
         }
     }
 
-    // one output pixel on its own (pixel-strided lanes); prep = window_ok
-    __device__ __forceinline__ static bool px_prep(const ItemRec &it) { return window_ok(it); }
-    __device__ __forceinline__ static void load_px(const ItemRec &it, bool win, int oy, int ox,
-                                                   float (&r)[C])
+    // one output pixel on its own (pixel-strided lanes); prep: 0 element
+    // loads, 1 windows, 2 windows at 32-bit offsets
+    __device__ __forceinline__ static int px_prep(const ItemRec &it)
     {
-        gsrc_t r0, r1;
-        float ay;
-        rows(it, oy, r0, r1, ay);
-        pixel(it, r0, r1, ay, ox, win, r);
+        return !window_ok(it) ? 0 : (it.flags & IF_SMALL_FRAME) ? 2 : 1;
     }
-
-    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int n,
-                                                float (&r)[kUnitPx][C])
+    __device__ __forceinline__ static void load_pxs(const ItemRec &it, int prep, const int (&oy)[kUnitPx],
+                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
     {
-        gsrc_t r0, r1;
-        float ay;
-        rows(it, oy, r0, r1, ay);
-        const bool win = window_ok(it);
+        if constexpr (DT == DT_U8) {
+            if (prep == 2) {
 #pragma unroll
-        for (int i = 0; i < kUnitPx; ++i) {
-            if (i < n) {
-                pixel(it, r0, r1, ay, ox0 + i, win, r[i]);
-            } else {
+                for (int i = 0; i < kUnitPx; ++i) {
+                    uint32_t o0, o1;
+                    float ay;
+                    rows_off(it, oy[i], o0, o1, ay);
+                    pixel_off(it, o0, o1, ay, ox[i], r[i]);
+                }
+                return;
+            }
+            if (prep == 1) {
 #pragma unroll
-                for (int c = 0; c < C; ++c)
-                    r[i][c] = 0.0f;
+                for (int i = 0; i < kUnitPx; ++i) {
+                    gsrc_t r0, r1;
+                    float ay;
+                    rows(it, oy[i], r0, r1, ay);
+                    pixel(it, r0, r1, ay, ox[i], true, r[i]);
+                }
+                return;
             }
         }
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i) {
+            gsrc_t r0, r1;
+            float ay;
+            rows(it, oy[i], r0, r1, ay);
+            pixel(it, r0, r1, ay, ox[i], false, r[i]);
+        }
+    }
+
+    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int,
+                                                float (&r)[kUnitPx][C])
+    {
+        load_unit_pxs<ReadCropResize, C>(it, oy, ox0, r);
     }
 };
 
@@ -412,26 +470,24 @@ struct ReadCropNearest {
             r[c] = load_elem<DT>(row + (sx * C + c) * ES);
     }
     __device__ __forceinline__ static bool px_prep(const ItemRec &it) { return window_ok(it); }
-    __device__ __forceinline__ static void load_px(const ItemRec &it, bool win, int oy, int ox, float (&r)[C])
+    __device__ __forceinline__ static void load_pxs(const ItemRec &it, bool win, const int (&oy)[kUnitPx],
+                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
     {
-        pixel(it, row_of(it, oy), ox, win, r);
+        if (win) {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+                pixel(it, row_of(it, oy[i]), ox[i], true, r[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+                pixel(it, row_of(it, oy[i]), ox[i], false, r[i]);
+        }
     }
 
-    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int n,
+    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int,
                                                 float (&r)[kUnitPx][C])
     {
-        gsrc_t row = row_of(it, oy);
-        const bool win = window_ok(it);
-#pragma unroll
-        for (int i = 0; i < kUnitPx; ++i) {
-            if (i < n) {
-                pixel(it, row, ox0 + i, win, r[i]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    r[i][c] = 0.0f;
-            }
-        }
+        load_unit_pxs<ReadCropNearest, C>(it, oy, ox0, r);
     }
 };
 
@@ -464,12 +520,6 @@ struct ReadNV12 {
     static_assert(C == 3, "NV12 reads give three channels");
     static constexpr int kind = RD_NV12;
     static constexpr int elem_size = 1;
-
-    __device__ __forceinline__ static bool px_prep(const ItemRec &) { return false; }
-    __device__ __forceinline__ static void load_px(const ItemRec &it, bool, int oy, int ox, float (&r)[C])
-    {
-        nv12_pixel(it, it.x + ox, it.y + oy, r);
-    }
 
     // A whole unit of a frame whose base, pitch and ROI column are
     // multiples of 4 (IF_SRC_VEC) reads its 4 luma bytes and the 2 chroma
@@ -530,37 +580,49 @@ struct ReadNV12Resize {
         return !last_chroma_row || ((it.x + it.w - 1) & ~1) + 8 <= (int)it.fw;
     }
 
-    // the taps at absolute columns X0 and X1 = X0 or X0 + 1 of absolute
-    // source row Y, from a luma and a chroma window
-    __device__ __forceinline__ static void row_taps(const ItemRec &it, int Y, int X0, int X1, float (&a)[3],
-                                                    float (&b)[3])
+    // the taps at absolute columns X0 and X0 + 1 of absolute source row Y,
+    // from a luma and a chroma window (a right tap clamped onto the left one
+    // takes weight 0 on whatever follows, see ReadCropResize)
+    template <bool Small>
+    __device__ __forceinline__ static void row_taps(const ItemRec &it, int Y, int X0, float (&a)[3], float (&b)[3])
     {
         gsrc_t base = (gsrc_t)it.src;
-        const uint64_t la = (uint64_t)(uintptr_t)(base + (int64_t)Y * it.pitch + X0);
-        const FK_GLOBAL uint32_t *lp = (const FK_GLOBAL uint32_t *)(la & ~(uint64_t)3);
-        const uint32_t lw = __builtin_amdgcn_alignbyte(lp[1], lp[0], (uint32_t)(la & 3));
         const int c0 = X0 & ~1;
-        const uint64_t ca = (uint64_t)(uintptr_t)(base + ((int64_t)it.fh + (Y >> 1)) * it.pitch + c0);
-        const FK_GLOBAL uint32_t *cp = (const FK_GLOBAL uint32_t *)(ca & ~(uint64_t)3);
-        const uint32_t cw = __builtin_amdgcn_alignbyte(cp[1], cp[0], (uint32_t)(ca & 3));
-        const int dl = X1 - X0;          // 0 or 1
-        const int dc = (X1 & ~1) - c0;   // 0 or 2
+        uint32_t lw, cw;
+        if constexpr (Small) {  // 32-bit offsets from the (uniform) frame base
+            const uint32_t lo = __umul24((uint32_t)Y, (uint32_t)it.pitch) + (uint32_t)X0;
+            const uint32_t co = __umul24((uint32_t)it.fh + ((uint32_t)Y >> 1), (uint32_t)it.pitch) + (uint32_t)c0;
+            const FK_GLOBAL uint32_t *lp = (const FK_GLOBAL uint32_t *)(base + (uint64_t)(lo & ~3u));
+            const FK_GLOBAL uint32_t *cp = (const FK_GLOBAL uint32_t *)(base + (uint64_t)(co & ~3u));
+            lw = __builtin_amdgcn_alignbyte(lp[1], lp[0], lo & 3u);
+            cw = __builtin_amdgcn_alignbyte(cp[1], cp[0], co & 3u);
+        } else {
+            const uint64_t la = (uint64_t)(uintptr_t)(base + (int64_t)Y * it.pitch + X0);
+            const FK_GLOBAL uint32_t *lp = (const FK_GLOBAL uint32_t *)(la & ~(uint64_t)3);
+            lw = __builtin_amdgcn_alignbyte(lp[1], lp[0], (uint32_t)(la & 3));
+            const uint64_t ca = (uint64_t)(uintptr_t)(base + ((int64_t)it.fh + (Y >> 1)) * it.pitch + c0);
+            const FK_GLOBAL uint32_t *cp = (const FK_GLOBAL uint32_t *)(ca & ~(uint64_t)3);
+            cw = __builtin_amdgcn_alignbyte(cp[1], cp[0], (uint32_t)(ca & 3));
+        }
+        // an odd left tap's right neighbour belongs to the next chroma pair
+        const uint32_t cr = (X0 & 1) ? cw >> 16 : cw;
         nv12_to_bgr((float)(lw & 0xffu), (float)(cw & 0xffu), (float)((cw >> 8) & 0xffu), a);
-        nv12_to_bgr((float)((lw >> (8 * dl)) & 0xffu), (float)((cw >> (8 * dc)) & 0xffu),
-                    (float)((cw >> (8 * dc + 8)) & 0xffu), b);
+        nv12_to_bgr((float)((lw >> 8) & 0xffu), (float)(cr & 0xffu), (float)((cr >> 8) & 0xffu), b);
     }
 
-    // output column ox of the output row whose source rows are y0, y1
-    __device__ __forceinline__ static void pixel(const ItemRec &it, int y0, int y1, float ay, int ox, bool win,
-                                                 float (&r)[C])
+    // output pixel (ox, oy); Prep as px_prep gives it
+    template <int Prep>
+    __device__ __forceinline__ static void pixel(const ItemRec &it, int oy, int ox, float (&r)[C])
     {
-        int x0, x1;
-        float ax;
+        int x0, x1, y0, y1;
+        float ax, ay;
+        bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
         bilinear_coord(ox, it.sx, it.w, x0, x1, ax);
         float p00[3], p01[3], p10[3], p11[3];
-        if (win) {
-            row_taps(it, it.y + y0, it.x + x0, it.x + x1, p00, p01);
-            row_taps(it, it.y + y1, it.x + x0, it.x + x1, p10, p11);
+        if constexpr (Prep != 0) {
+            row_taps<Prep == 2>(it, it.y + y0, it.x + x0, p00, p01);
+            row_taps<Prep == 2>(it, it.y + y1, it.x + x0, p10, p11);
+            ax = x1 == x0 ? 0.0f : ax;
         } else {
             nv12_pixel(it, it.x + x0, it.y + y0, p00);
             nv12_pixel(it, it.x + x1, it.y + y0, p01);
@@ -574,32 +636,36 @@ struct ReadNV12Resize {
             r[c] = fmaf(ay, bot - top, top);
         }
     }
-    __device__ __forceinline__ static bool px_prep(const ItemRec &it) { return window_ok(it); }
-    __device__ __forceinline__ static void load_px(const ItemRec &it, bool win, int oy, int ox, float (&r)[C])
+    template <int Prep>
+    __device__ __forceinline__ static void pixels(const ItemRec &it, const int (&oy)[kUnitPx],
+                                                  const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
     {
-        int y0, y1;
-        float ay;
-        bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
-        pixel(it, y0, y1, ay, ox, win, r);
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i)
+            pixel<Prep>(it, oy[i], ox[i], r[i]);
+    }
+    // 0 byte loads, 1 windows, 2 windows at 32-bit offsets (a frame of 1.5
+    // heights below 4 GiB)
+    __device__ __forceinline__ static int px_prep(const ItemRec &it)
+    {
+        const bool small = (it.flags & IF_SMALL_FRAME) && (uint64_t)it.pitch * it.fh < 0x80000000ull;
+        return !window_ok(it) ? 0 : small ? 2 : 1;
+    }
+    __device__ __forceinline__ static void load_pxs(const ItemRec &it, int prep, const int (&oy)[kUnitPx],
+                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
+    {
+        if (prep == 2)
+            pixels<2>(it, oy, ox, r);
+        else if (prep == 1)
+            pixels<1>(it, oy, ox, r);
+        else
+            pixels<0>(it, oy, ox, r);
     }
 
-    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int n,
+    __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int,
                                                 float (&r)[kUnitPx][C])
     {
-        int y0, y1;
-        float ay;
-        bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
-        const bool win = window_ok(it);
-#pragma unroll
-        for (int i = 0; i < kUnitPx; ++i) {
-            if (i < n) {
-                pixel(it, y0, y1, ay, ox0 + i, win, r[i]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    r[i][c] = 0.0f;
-            }
-        }
+        load_unit_pxs<ReadNV12Resize, C>(it, oy, ox0, r);
     }
 };
 
@@ -657,14 +723,17 @@ struct OpSub {
             px[c] = px[c] - k[PerCh ? S + c : S];
     }
 };
+// Division by the constants of the DivRec32 at byte offset kDivRecOffset of
+// the table (defined with the run-time ops below).
+template <int K, int P, int C>
+__device__ __forceinline__ void div_values(float (&v)[K][P][C], const FK_CONST DivRec32 *q);
 template <int S, bool PerCh>
 struct OpDiv {
-    template <int C>
-    __device__ __forceinline__ static void exec(float (&px)[C], const FK_CONST float *k)
+    static constexpr bool tile_op = true;
+    template <int K, int C>
+    __device__ __forceinline__ static void exec_tile(float (&v)[K][kUnitPx][C], const FK_CONST float *k)
     {
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            px[c] = px[c] / k[PerCh ? S + c : S];
+        div_values(v, (const FK_CONST DivRec32 *)((const FK_CONST uint8_t *)k + kDivRecOffset));
     }
 };
 // Contracted Mul followed by Add (Neg = false) or Sub (Neg = true).
@@ -1338,7 +1407,8 @@ __device__ __forceinline__ void own_registers(float (&v)[G][kUnitPx][C])
 // whole tile fits, else the largest group that compiles without scratch
 // (from the kernels' scratch sizes): 4 units of 3 channels, 2 of 4; 2 for
 // the run-time op list into planar fp32 (91 registers where 4 would leave
-// four waves a SIMD), for the NV12 resize read and for the nearest read.
+// four waves a SIMD), for the NV12 resize, the nearest and the fp32 resize
+// reads.
 template <class Read, class Compute, class Write, int C, int K>
 constexpr int unit_group()
 {
@@ -1349,6 +1419,8 @@ constexpr int unit_group()
         g = 2;
     if ((Read::kind == RD_NV12_RESIZE || (rt && Read::kind == RD_CROP_NEAREST)) && g > 2)
         g = 2;  // four converted taps per pixel; 64-bit source indices
+    if (rt && Read::kind == RD_CROP_RESIZE && Read::elem_size == 4 && C == 3 && g > 2)
+        g = 2;  // 12 loads in flight per pixel
     return K < g ? K : g;
 }
 
@@ -1462,24 +1534,27 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 // instruction.  Tiles are those of k_transform (T * K units = 4 T K
 // pixels); the per-pixel planar stores of consecutive lanes are
 // consecutive.
-// Store pixel i's C channels of v to its planar output position.
+// Store pixel p's C channels to its planar output position: a 32-bit offset
+// from each plane's (uniform) base.
 template <int DO, int C>
-__device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, const ItemRec &it, int oy,
-                                                int ox, const float (&v)[C])
+__device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint32_t p, const float (&v)[C])
 {
     constexpr int ES = DSize<DO>::v;
-    // below ow * oh < 2^32
-    const uint32_t p = __umul24((uint32_t)oy, (uint32_t)it.ow) + (uint32_t)ox;
 #pragma unroll
-    for (int c = 0; c < C; ++c)
-        store_elem<DO>(dst + (c * plane + (int64_t)p) * ES, v[c]);
+    for (int c = 0; c < C; ++c) {
+        uint64_t base = (uint64_t)(uintptr_t)dst + (uint64_t)(c * plane * ES);
+        asm("" : "+s"(base));  // uniform: keep the add of the lane's offset apart
+        store_elem<DO>((gdst_t)base + (uint64_t)(p * ES), v[c]);  // p < 2^28
+    }
 }
 
 // The chain on 4 gathered pixels per lane (v), then their planar stores;
-// oy[i] < 0 marks a lane's pixel outside the tile.
+// p[i] = kNoPixel marks a lane's pixel outside the tile.
+constexpr uint32_t kNoPixel = 0xffffffffu;
+
 template <class Compute, int DO, int C>
 __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it, float (&v)[1][kUnitPx][C],
-                                               const int (&oy)[kUnitPx], const int (&ox)[kUnitPx])
+                                               const uint32_t (&p)[kUnitPx])
 {
     if constexpr (C >= 3) {
         // run-time tier: the chain's net channel swap, applied at the read
@@ -1498,44 +1573,55 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
     const int64_t plane = (int64_t)it.ow * it.oh;
 #pragma unroll
     for (int i = 0; i < kUnitPx; ++i)
-        if (oy[i] >= 0)
-            store_planar_px<DO, C>((gdst_t)it.dst, plane, it, oy[i], ox[i], v[0][i]);
+        if (p[i] != kNoPixel)
+            store_planar_px<DO, C>((gdst_t)it.dst, plane, p[i], v[0][i]);
 }
 
 // One tile of pixel-strided lanes: output pixels [pbase, pbase + 4 T K)
-// of the item, pixel pbase + q T + t on lane t.
+// of the item, pixel pbase + q T + t on lane t.  The row of a lane's first
+// pixel comes from a division, the next ones from steps of T pixels
+// (T / ow rows and T % ow columns, one carry).
+//
+// About 200 VALU instructions a pixel held 778 u8 crops of 24 4K frames (0.49
+// GB in 32-byte sectors, 94 us at a large copy's rate) at 113 us.  With the
+// row steps, taps at 32-bit offsets from the frame base, byte positions that
+// do not depend on the clamp, and the division by reciprocal it takes 94 us;
+// 256 NV12 crops 15.5 -> 12.8 us.
 template <class Read, class Compute, int DO, int C, int K>
 __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint32_t ubase, int T, int tid)
 {
-    const uint32_t npx = (uint32_t)it.ow * (uint32_t)it.oh;  // < 2^32
-    const uint32_t pbase = ubase * kUnitPx;
-    const RowDiv rowdiv((uint32_t)it.ow);  // exact below 2^28 pixels
-    const bool big = npx >= (1u << 28);
-    const bool prep = Read::px_prep(it);
+    const uint32_t ow = (uint32_t)it.ow;
+    const uint32_t npx = ow * (uint32_t)it.oh;  // <= 2^28
+    const RowDiv rowdiv(ow);
+    const uint32_t step_rows = rowdiv((uint32_t)T), step_cols = (uint32_t)T - __umul24(step_rows, ow);
+    const auto prep = Read::px_prep(it);
+    uint32_t at = ubase * kUnitPx + (uint32_t)tid;
+    uint32_t row = rowdiv(at), col = at - __umul24(row, ow);
 
     // groups of 4 pixels per lane, one after another: registers do not
     // grow with K (K only sizes the tile)
     for (int j = 0; j < K; ++j) {
         float v[1][kUnitPx][C];
+        uint32_t p[kUnitPx];
         int oy[kUnitPx], ox[kUnitPx];
 #pragma unroll
         for (int i = 0; i < kUnitPx; ++i) {
-            const uint32_t q = (uint32_t)(j * kUnitPx + i);
-            const uint32_t p = pbase + q * (uint32_t)T + (uint32_t)tid;
-            if (p < npx && p >= pbase) {
-                const uint32_t row = big ? p / (uint32_t)it.ow : rowdiv(p);
-                oy[i] = (int)row;
-                ox[i] = (int)(p - __umul24(row, (uint32_t)it.ow));
-                Read::load_px(it, prep, oy[i], ox[i], v[0][i]);
-            } else {
-                oy[i] = -1;
-                ox[i] = 0;
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    v[0][i][c] = 0.0f;
+            // lanes past the item read its first pixel and store nothing: no
+            // branch per pixel, so that the gathers are in flight together
+            const bool in = at < npx;
+            p[i] = in ? at : kNoPixel;
+            oy[i] = in ? (int)row : 0;
+            ox[i] = in ? (int)col : 0;
+            at += (uint32_t)T;
+            row += step_rows;
+            col += step_cols;
+            if (col >= ow) {
+                col -= ow;
+                ++row;
             }
         }
-        chain_store_px<Compute, DO, C>(a, it, v, oy, ox);
+        Read::load_pxs(it, prep, oy, ox, v[0]);
+        chain_store_px<Compute, DO, C>(a, it, v, p);
     }
 }
 
@@ -1669,18 +1755,17 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_lds(const KArgs a)
             const uint32_t p1 = min(pend, (r0 + nr) * ow);
             for (uint32_t pb = p0; pb < p1; pb += (uint32_t)kUnitPx * (uint32_t)T) {
                 float v[1][kUnitPx][C];
-                int oy[kUnitPx], ox[kUnitPx];
+                uint32_t px[kUnitPx];
 #pragma unroll
                 for (int i = 0; i < kUnitPx; ++i) {
                     const uint32_t p = pb + (uint32_t)(i * T + tid);
+                    px[i] = p < p1 ? p : kNoPixel;
                     if (p < p1) {
                         const uint32_t row = rowdiv(p);
-                        oy[i] = (int)row;
-                        ox[i] = (int)(p - __umul24(row, ow));
                         int x0, x1, y0, y1;
                         float ax, ay;
-                        bilinear_coord(ox[i], it.sx, it.w, x0, x1, ax);
-                        bilinear_coord(oy[i], it.sy, it.h, y0, y1, ay);
+                        bilinear_coord((int)(p - __umul24(row, ow)), it.sx, it.w, x0, x1, ax);
+                        bilinear_coord((int)row, it.sy, it.h, y0, y1, ay);
                         const uint32_t off = (uint32_t)(it.x + x0) * C - g.start;
                         const uint32_t top = 2u * (row - r0) * g.stride + off;
                         uint32_t tw[2], bw[2];
@@ -1688,14 +1773,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_lds(const KArgs a)
                         lds_window(lds, top + g.stride, bw);
                         Read::lerp_windows(tw, bw, x1 == x0, ax, ay, v[0][i]);
                     } else {
-                        oy[i] = -1;
-                        ox[i] = 0;
 #pragma unroll
                         for (int c = 0; c < C; ++c)
                             v[0][i][c] = 0.0f;
                     }
                 }
-                chain_store_px<Compute, DO, C>(a, it, v, oy, ox);
+                chain_store_px<Compute, DO, C>(a, it, v, px);
             }
         }
     }

@@ -380,6 +380,12 @@ extern "C" fk_status fk_plan_create(const fk_chain_desc *chain, int32_t max_batc
                         : o.tier == FK_TIER_AUTO && !stats ? match_static(&p->chain, consts, sn)
                                                            : FAM_RUNTIME;
         p->static_n = sn;
+        if (p->family == FAM_NORMALIZE) {
+            const float std4[4] = {consts[4], consts[5], consts[6], 1.0f};
+            const DivRec32 q = div_record(std4, 3);
+            consts.resize((kDivRecOffset + sizeof q) / sizeof(float), 0.0f);
+            std::memcpy((char *)consts.data() + kDivRecOffset, &q, sizeof q);
+        }
         normalise_chain(&p->chain, o.strict_fp != 0, p->ops, p->swap);
         p->cfg = o.config_source == FK_CONFIG_MANUAL ? o.manual : default_config(p);
         if (!runs_op_list(p)) {

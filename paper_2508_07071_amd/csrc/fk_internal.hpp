@@ -84,6 +84,9 @@ struct DivRec32 {       // 64 bytes
     uint32_t thr;
     uint32_t pad[3];
 };
+// The compile-time normalise chain's division record, in its constant table
+// after the chain's seven constants.
+constexpr int kDivRecOffset = 32;
 struct DivRec64 {       // 112 bytes
     double zh[4], zl[4], d[4];
     uint32_t thr;
