@@ -339,8 +339,14 @@ def out_shape(chain: dict, item: dict) -> tuple:
 
 
 def stream_handle(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    """The hipStream_t of `stream`, or of torch's current stream.  The current
+    stream's handle is asked for directly: torch.cuda.current_stream() builds
+    a Stream object first, 2.8 us of a 6.6 us fk_run call."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ------------------------------------------------------------- C ABI calls --
