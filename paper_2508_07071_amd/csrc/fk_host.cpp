@@ -678,11 +678,13 @@ static fk_status launch_compact(const fk_plan *p, const fk_item *items, int32_t 
     a.inl_total_tiles = a.inl_tiles_per_item * (uint32_t)n;
     a.inl_dst_stride = (int64_t)stride;
     // template flags: frame base and pitch dword-aligned; outputs aligned
-    // for every item (base and stride multiples of 16)
-    t.flags = 0;
+    // for every item (base and stride multiples of 16); contiguous as item 0
+    // is (every item then spans the frame's whole rows)
+    const bool one_row = (t.flags & IF_CONTIG) != 0;
+    t.flags = one_row ? (int32_t)IF_CONTIG : 0;
     if ((uintptr_t)items[0].src.ptr % 4 == 0 && items[0].src.pitch_bytes % 4 == 0)
         t.flags |= IF_SRC_VEC;
-    if (t.ow % kUnitPx == 0 && (uintptr_t)items[0].dst % 16 == 0 && a.inl_dst_stride % 16 == 0)
+    if ((one_row || t.ow % kUnitPx == 0) && (uintptr_t)items[0].dst % 16 == 0 && a.inl_dst_stride % 16 == 0)
         t.flags |= IF_DST_VEC;
     if (small_frame(items[0].src))
         t.flags |= IF_SMALL_FRAME;

@@ -64,3 +64,27 @@ def test_ragged_compile_time_chain_and_graph():
                 got = H.host(p.run(dev, items))
                 for a, r in zip(got, refs):
                     H.assert_bitexact(a, r["out"], f"graph {graph}")
+
+
+@pytest.mark.parametrize("w,h,layout", [(61, 5, "packed"), (61, 7, "planar"), (63, 1, "packed"), (257, 3, "planar"),
+                                        (64, 4, "packed")])
+def test_strips_of_one_frame(w, h, layout):
+    """More whole-row strips of one frame than the full kernel-argument form
+    holds, outputs at a constant stride."""
+    g = datagen.rng(w)
+    n, c = 45, 3
+    ch = {"read": {"kind": "plain", "dtype": "u8", "channels": c, "out_w": 0, "out_h": 0},
+          "ops": [{"kind": "mul", "k": [0.5]}, {"kind": "div", "k": [3.0]}],
+          "write": {"dtype": "f32", "layout": layout}}
+    fr = datagen.frame(g, n * h, w, c)
+    items = [{"frame": 0, "x": 0, "y": i * h, "w": w, "h": h} for i in range(n)]
+    refs = oracle.run_chain(ch, [fr], items)
+    out = torch.full((n,) + tuple(fk.out_shape(ch, items[0])), float("nan"), device="cuda")
+    for cfg in ((64, 1), (256, 1), (128, 8)):
+        out.fill_(float("nan"))
+        with H.Plan(ch, n, strict=True, tier=1) as p:
+            p.set_config(*cfg)
+            p.run(H.to_dev([fr]), items, outs=[out[i] for i in range(n)])
+        got = out.cpu().numpy()
+        for i, r in enumerate(refs):
+            H.assert_bitexact(got[i], r["out"], f"{cfg} strip {i}")
