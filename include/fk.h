@@ -274,19 +274,21 @@ fk_status fk_plan_get_tier(const fk_plan *plan, int32_t *is_static);
 /* Fused execution (asynchronous on `stream`, a hipStream_t; NULL = the
  * default stream): one horizontally and vertically fused launch covering
  * all `n_items` items (1 <= n_items <= max_batch).  The items' parameters
- * travel in the kernel arguments (up to 32 items; up to 312 items that
- * share one frame and one output size and whose outputs lie at a constant
- * stride), else in a device run table that a small upload kernel fills
- * on the same stream just before the launch.  A constant-stride batch of
- * more than 312 items (not a stats write) goes out as consecutive launches
- * of up to 312 items.  `items` is copied before the call returns; a
+ * travel in the kernel arguments (up to 32 items; of items that share one
+ * frame geometry and one output size and whose outputs lie at a constant
+ * stride, up to 312 of one frame, 624 where the read is 1:1, or 156 of
+ * several frames), else in a device run table that a small upload kernel
+ * fills on the same stream just before the launch.  A constant-stride batch
+ * beyond these (not a stats write; of several frames, up to twice its limit)
+ * goes out as consecutive launches.  `items` is copied before the call returns; a
  * table run first waits for the run that used the same table slot four
  * table runs earlier.
  *
  * Under the caller's stream capture (hipStreamBeginCapture on `stream`,
  * e.g. to replay several runs as one graph: a graph launch costs about as
  * much host time as several direct launches, so one graph per run does not
- * pay), a run whose items travel in the kernel arguments is captured as
+ * pay), a run of up to 32 items, or of items of one frame in the kernel
+ * arguments (a stats write: up to 312), is captured as
  * its kernel launches, parameters included; any other run returns
  * FK_ERR_UNSUPPORTED before touching the stream (its table is staged in
  * host memory that later runs rewrite), and so does a plan with use_graph

@@ -240,29 +240,24 @@ struct ReadCropResize {
         }
     }
 
-    // bytes [0, 2C) of the tap pair at p's dword-aligned window, sh = the
+    // bytes [0, 2C) of the tap pair in its dword-aligned window, sh = the
     // pair's offset in it (0..3)
-    __device__ __forceinline__ static void window(const FK_GLOBAL uint32_t *p, uint32_t sh, uint32_t (&d)[2])
+    __device__ __forceinline__ static void cut(const uint32_t (&w)[WB / 4], uint32_t sh, uint32_t (&d)[2])
     {
-        if constexpr (WB == 8) {
-            const uint32_t w0 = p[0], w1 = p[1];
-            d[0] = __builtin_amdgcn_alignbyte(w1, w0, sh);
+        d[0] = __builtin_amdgcn_alignbyte(w[1], w[0], sh);
+        if constexpr (WB == 8)
             d[1] = 0;
-        } else {
-            const uint32_t w0 = p[0], w1 = p[1], w2 = p[2];
-            d[0] = __builtin_amdgcn_alignbyte(w1, w0, sh);
-            d[1] = __builtin_amdgcn_alignbyte(w2, w1, sh);
-        }
+        else
+            d[1] = __builtin_amdgcn_alignbyte(w[2], w[1], sh);
     }
     __device__ __forceinline__ static void window_at(uint64_t addr, uint32_t (&d)[2])
     {
-        window((const FK_GLOBAL uint32_t *)(addr & ~(uint64_t)3), (uint32_t)(addr & 3), d);
-    }
-    // the same at a 32-bit offset from the (dword-aligned, uniform) frame
-    // base: the load takes the base as a scalar, no 64-bit address per lane
-    __device__ __forceinline__ static void window_off(gsrc_t base, uint32_t off, uint32_t (&d)[2])
-    {
-        window((const FK_GLOBAL uint32_t *)(base + (uint64_t)(off & ~3u)), off & 3u, d);
+        const FK_GLOBAL uint32_t *p = (const FK_GLOBAL uint32_t *)(addr & ~(uint64_t)3);
+        uint32_t w[WB / 4];
+#pragma unroll
+        for (int j = 0; j < WB / 4; ++j)
+            w[j] = p[j];
+        cut(w, (uint32_t)(addr & 3), d);
     }
 
     __device__ __forceinline__ static float byte_at(const uint32_t (&d)[2], int k)
@@ -320,8 +315,9 @@ struct ReadCropResize {
         }
     }
 
-    // output pixel (ox, oy) of an item that takes windows, in a frame of
-    // 32-bit offsets (IF_SMALL_FRAME); o0, o1: its source rows' offsets
+    // Items that take windows in a frame of 32-bit offsets (IF_SMALL_FRAME):
+    // loads at an offset from the dword-aligned, uniform frame base, which
+    // they take as a scalar; o0, o1: the source rows' offsets of output row oy
     __device__ __forceinline__ static void rows_off(const ItemRec &it, int oy, uint32_t &o0, uint32_t &o1,
                                                     float &ay)
     {
@@ -331,17 +327,41 @@ struct ReadCropResize {
         o0 = __umul24((uint32_t)(it.y + y0), (uint32_t)it.pitch) + col;
         o1 = __umul24((uint32_t)(it.y + y1), (uint32_t)it.pitch) + col;
     }
-    __device__ __forceinline__ static void pixel_off(const ItemRec &it, uint32_t o0, uint32_t o1, float ay, int ox,
-                                                     float (&r)[C])
+    // the four pixels' windows first, then their values: all eight loads in
+    // flight together
+    __device__ __forceinline__ static void pixels_off(const ItemRec &it, const int (&oy)[kUnitPx],
+                                                      const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
     {
-        int x0, x1;
-        float ax;
-        bilinear_coord(ox, it.sx, it.w, x0, x1, ax);
-        const uint32_t x = __umul24((uint32_t)x0, (uint32_t)C);
-        uint32_t t[2], b[2];
-        window_off((gsrc_t)it.src, o0 + x, t);
-        window_off((gsrc_t)it.src, o1 + x, b);
-        lerp_windows(t, b, x1 == x0, ax, ay, r);
+        uint32_t w[kUnitPx][2][WB / 4], sh[kUnitPx][2];
+        float ax[kUnitPx], ay[kUnitPx];
+        bool clamped[kUnitPx];
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i) {
+            uint32_t o[2];
+            int x0, x1;
+            rows_off(it, oy[i], o[0], o[1], ay[i]);
+            bilinear_coord(ox[i], it.sx, it.w, x0, x1, ax[i]);
+            clamped[i] = x1 == x0;
+            const uint32_t x = __umul24((uint32_t)x0, (uint32_t)C);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const uint32_t off = o[k] + x;
+                const FK_GLOBAL uint32_t *p =
+                    (const FK_GLOBAL uint32_t *)((gsrc_t)it.src + (uint64_t)(off & ~3u));
+                sh[i][k] = off & 3u;
+#pragma unroll
+                for (int j = 0; j < WB / 4; ++j)
+                    w[i][k][j] = p[j];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i) {
+            uint32_t d[2][2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                cut(w[i][k], sh[i][k], d[k]);
+            lerp_windows(d[0], d[1], clamped[i], ax[i], ay[i], r[i]);
+        }
     }
 
     // source rows of output row oy, and the vertical weight.  A frame
@@ -374,13 +394,7 @@ struct ReadCropResize {
     {
         if constexpr (DT == DT_U8) {
             if (prep == 2) {
-#pragma unroll
-                for (int i = 0; i < kUnitPx; ++i) {
-                    uint32_t o0, o1;
-                    float ay;
-                    rows_off(it, oy[i], o0, o1, ay);
-                    pixel_off(it, o0, o1, ay, ox[i], r[i]);
-                }
+                pixels_off(it, oy, ox, r);
                 return;
             }
             if (prep == 1) {
@@ -580,55 +594,48 @@ struct ReadNV12Resize {
         return !last_chroma_row || ((it.x + it.w - 1) & ~1) + 8 <= (int)it.fw;
     }
 
-    // the taps at absolute columns X0 and X0 + 1 of absolute source row Y,
-    // from a luma and a chroma window (a right tap clamped onto the left one
-    // takes weight 0 on whatever follows, see ReadCropResize)
+    // the luma and chroma windows of the taps at absolute columns X0 and X0 + 1
+    // of absolute source row Y, as loaded (w: luma, chroma; sh: their offsets)
     template <bool Small>
-    __device__ __forceinline__ static void row_taps(const ItemRec &it, int Y, int X0, float (&a)[3], float (&b)[3])
+    __device__ __forceinline__ static void row_windows(const ItemRec &it, int Y, int X0, uint32_t (&w)[2][2],
+                                                       uint32_t (&sh)[2])
     {
         gsrc_t base = (gsrc_t)it.src;
-        const int c0 = X0 & ~1;
-        uint32_t lw, cw;
-        if constexpr (Small) {  // 32-bit offsets from the (uniform) frame base
-            const uint32_t lo = __umul24((uint32_t)Y, (uint32_t)it.pitch) + (uint32_t)X0;
-            const uint32_t co = __umul24((uint32_t)it.fh + ((uint32_t)Y >> 1), (uint32_t)it.pitch) + (uint32_t)c0;
-            const FK_GLOBAL uint32_t *lp = (const FK_GLOBAL uint32_t *)(base + (uint64_t)(lo & ~3u));
-            const FK_GLOBAL uint32_t *cp = (const FK_GLOBAL uint32_t *)(base + (uint64_t)(co & ~3u));
-            lw = __builtin_amdgcn_alignbyte(lp[1], lp[0], lo & 3u);
-            cw = __builtin_amdgcn_alignbyte(cp[1], cp[0], co & 3u);
-        } else {
-            const uint64_t la = (uint64_t)(uintptr_t)(base + (int64_t)Y * it.pitch + X0);
-            const FK_GLOBAL uint32_t *lp = (const FK_GLOBAL uint32_t *)(la & ~(uint64_t)3);
-            lw = __builtin_amdgcn_alignbyte(lp[1], lp[0], (uint32_t)(la & 3));
-            const uint64_t ca = (uint64_t)(uintptr_t)(base + ((int64_t)it.fh + (Y >> 1)) * it.pitch + c0);
-            const FK_GLOBAL uint32_t *cp = (const FK_GLOBAL uint32_t *)(ca & ~(uint64_t)3);
-            cw = __builtin_amdgcn_alignbyte(cp[1], cp[0], (uint32_t)(ca & 3));
+        const int col[2] = {X0, X0 & ~1};
+        const int row[2] = {Y, (int)it.fh + (Y >> 1)};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const FK_GLOBAL uint32_t *p;
+            if constexpr (Small) {  // 32-bit offsets from the (uniform) frame base
+                const uint32_t off = __umul24((uint32_t)row[k], (uint32_t)it.pitch) + (uint32_t)col[k];
+                p = (const FK_GLOBAL uint32_t *)(base + (uint64_t)(off & ~3u));
+                sh[k] = off & 3u;
+            } else {
+                const uint64_t a = (uint64_t)(uintptr_t)(base + (int64_t)row[k] * it.pitch + col[k]);
+                p = (const FK_GLOBAL uint32_t *)(a & ~(uint64_t)3);
+                sh[k] = (uint32_t)(a & 3);
+            }
+            w[k][0] = p[0];
+            w[k][1] = p[1];
         }
+    }
+
+    // the two taps, converted (a right tap clamped onto the left one takes
+    // weight 0 on whatever follows, see ReadCropResize)
+    __device__ __forceinline__ static void row_taps(const uint32_t (&w)[2][2], const uint32_t (&sh)[2], bool odd,
+                                                    float (&a)[3], float (&b)[3])
+    {
+        const uint32_t lw = __builtin_amdgcn_alignbyte(w[0][1], w[0][0], sh[0]);
+        const uint32_t cw = __builtin_amdgcn_alignbyte(w[1][1], w[1][0], sh[1]);
         // an odd left tap's right neighbour belongs to the next chroma pair
-        const uint32_t cr = (X0 & 1) ? cw >> 16 : cw;
+        const uint32_t cr = odd ? cw >> 16 : cw;
         nv12_to_bgr((float)(lw & 0xffu), (float)(cw & 0xffu), (float)((cw >> 8) & 0xffu), a);
         nv12_to_bgr((float)((lw >> 8) & 0xffu), (float)(cr & 0xffu), (float)((cr >> 8) & 0xffu), b);
     }
 
-    // output pixel (ox, oy); Prep as px_prep gives it
-    template <int Prep>
-    __device__ __forceinline__ static void pixel(const ItemRec &it, int oy, int ox, float (&r)[C])
+    __device__ __forceinline__ static void lerp(const float (&p00)[3], const float (&p01)[3], const float (&p10)[3],
+                                                const float (&p11)[3], float ax, float ay, float (&r)[C])
     {
-        int x0, x1, y0, y1;
-        float ax, ay;
-        bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
-        bilinear_coord(ox, it.sx, it.w, x0, x1, ax);
-        float p00[3], p01[3], p10[3], p11[3];
-        if constexpr (Prep != 0) {
-            row_taps<Prep == 2>(it, it.y + y0, it.x + x0, p00, p01);
-            row_taps<Prep == 2>(it, it.y + y1, it.x + x0, p10, p11);
-            ax = x1 == x0 ? 0.0f : ax;
-        } else {
-            nv12_pixel(it, it.x + x0, it.y + y0, p00);
-            nv12_pixel(it, it.x + x1, it.y + y0, p01);
-            nv12_pixel(it, it.x + x0, it.y + y1, p10);
-            nv12_pixel(it, it.x + x1, it.y + y1, p11);
-        }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const float top = fmaf(ax, p01[c] - p00[c], p00[c]);
@@ -636,13 +643,37 @@ struct ReadNV12Resize {
             r[c] = fmaf(ay, bot - top, top);
         }
     }
+
+    // output pixels (ox, oy); Prep as px_prep gives it.  Pixel by pixel:
+    // all windows before the first value took 16 registers more and no less
+    // time.
     template <int Prep>
     __device__ __forceinline__ static void pixels(const ItemRec &it, const int (&oy)[kUnitPx],
                                                   const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
     {
 #pragma unroll
-        for (int i = 0; i < kUnitPx; ++i)
-            pixel<Prep>(it, oy[i], ox[i], r[i]);
+        for (int i = 0; i < kUnitPx; ++i) {
+            int x0, x1, y0, y1;
+            float ax, ay;
+            bilinear_coord(oy[i], it.sy, it.h, y0, y1, ay);
+            bilinear_coord(ox[i], it.sx, it.w, x0, x1, ax);
+            float p00[3], p01[3], p10[3], p11[3];
+            if constexpr (Prep != 0) {
+                uint32_t w[2][2], sh[2];
+                const bool odd = (it.x + x0) & 1;
+                row_windows<Prep == 2>(it, it.y + y0, it.x + x0, w, sh);
+                row_taps(w, sh, odd, p00, p01);
+                row_windows<Prep == 2>(it, it.y + y1, it.x + x0, w, sh);
+                row_taps(w, sh, odd, p10, p11);
+                ax = x1 == x0 ? 0.0f : ax;
+            } else {
+                nv12_pixel(it, it.x + x0, it.y + y0, p00);
+                nv12_pixel(it, it.x + x1, it.y + y0, p01);
+                nv12_pixel(it, it.x + x0, it.y + y1, p10);
+                nv12_pixel(it, it.x + x1, it.y + y1, p11);
+            }
+            lerp(p00, p01, p10, p11, ax, ay, r[i]);
+        }
     }
     // 0 byte loads, 1 windows, 2 windows at 32-bit offsets (a frame of 1.5
     // heights below 4 GiB)
@@ -1344,6 +1375,44 @@ __device__ __forceinline__ int find_item_guess(const FK_CONST uint32_t *tb, int 
     return lo;
 }
 
+// Item b of a compact batch: the template with the item's own fields.
+template <int Kind, int C, int ElemSize>
+__device__ __forceinline__ ItemRec compact_item(const KArgs &a, const FK_CONST KArgs *ka, int b)
+{
+    ItemRec it = load_item((const FK_CONST ItemRec *)ka->inl);
+    // whole dwords: a 16-bit load has no scalar form, and an item in vector
+    // registers costs the gathers their scalar frame base (256 NV12 crops
+    // 12.8 -> 17.6 us)
+    const FK_CONST uint32_t *recs = (const FK_CONST uint32_t *)(ka->inl + 64);
+    if (!rd_resizes(Kind) && a.inl_compact == CF_POINT) {
+        const uint32_t xy = recs[b];
+        it.x = (int32_t)(xy & 0xffffu);
+        it.y = (int32_t)(xy >> 16);
+    } else {
+        int at = 2 * b;  // the Roi16's first dword
+        if (a.inl_compact == CF_FRAME) {
+            at = 4 * b + 2;
+            it.src = (uint64_t)recs[4 * b] | ((uint64_t)recs[4 * b + 1] << 32);
+        }
+        const uint32_t xy = recs[at], wh = recs[at + 1];
+        it.x = (int32_t)(xy & 0xffffu);
+        it.y = (int32_t)(xy >> 16);
+        it.w = (int32_t)(wh & 0xffffu);
+        it.h = (int32_t)(wh >> 16);
+    }
+    it.dst += (uint64_t)b * (uint64_t)a.inl_dst_stride;
+    if constexpr (rd_bilinear(Kind)) {
+        // the same IEEE fp32 divisions the host performs for the table forms
+        it.sx = (float)it.w / (float)it.ow;
+        it.sy = (float)it.h / (float)it.oh;
+    }
+    // template bit: frame base and pitch dword-aligned; the ROI's column
+    // offset decides the rest
+    if ((it.x * C * ElemSize) % 4 != 0)
+        it.flags &= ~IF_SRC_VEC;
+    return it;
+}
+
 // The item owning `tile` (with the compact form's per-item fields filled
 // in), and the tile's first unit within it.
 template <class Read, int C>
@@ -1356,22 +1425,7 @@ __device__ __forceinline__ void tile_item(const KArgs &a, const FK_CONST KArgs *
     if (compact) {
         const int b = (int)(tile / a.inl_tiles_per_item);
         first_tile = (uint32_t)b * a.inl_tiles_per_item;
-        it = load_item(items);  // the template (item 0)
-        const FK_CONST Roi16 *roi = (const FK_CONST Roi16 *)(ka->inl + 64) + b;
-        it.x = roi->x;
-        it.y = roi->y;
-        it.w = roi->w;
-        it.h = roi->h;
-        it.dst += (uint64_t)b * (uint64_t)a.inl_dst_stride;
-        if constexpr (rd_bilinear(Read::kind)) {
-            // the same IEEE fp32 divisions the host performs for the table forms
-            it.sx = (float)it.w / (float)it.ow;
-            it.sy = (float)it.h / (float)it.oh;
-        }
-        // template bit: frame base and pitch dword-aligned; the ROI's
-        // column offset decides the rest
-        if ((it.x * C * Read::elem_size) % 4 != 0)
-            it.flags &= ~IF_SRC_VEC;
+        it = compact_item<Read::kind, C, Read::elem_size>(a, ka, b);
     } else {
         const int b = find_item_guess(tb, n_items, tile, total);
         it = load_item(items + b);
@@ -1543,7 +1597,9 @@ __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint3
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         uint64_t base = (uint64_t)(uintptr_t)dst + (uint64_t)(c * plane * ES);
-        asm("" : "+s"(base));  // uniform: keep the add of the lane's offset apart
+        // uniform: in scalar registers, apart from the lane's offset
+        base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         store_elem<DO>((gdst_t)base + (uint64_t)(p * ES), v[c]);  // p < 2^28
     }
 }
@@ -1821,13 +1877,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_loop_px(const KArgs a)
         if (compact) {
             b = (int)(tile / a.inl_tiles_per_item);
             first_tile = (uint32_t)b * a.inl_tiles_per_item;
-            it = load_item(items);
-            const FK_CONST Roi16 *roi = (const FK_CONST Roi16 *)(ka->inl + 64) + b;
-            it.x = roi->x;
-            it.y = roi->y;
-            it.w = roi->w;
-            it.h = roi->h;
-            it.dst += (uint64_t)b * (uint64_t)a.inl_dst_stride;
+            it = compact_item<RD_PLAIN, C, ES>(a, ka, b);
         } else {
             b = find_item_guess(tb, n_items, tile, total);
             it = load_item(items + b);
@@ -2178,19 +2228,7 @@ __device__ __forceinline__ void stats_slot_item(const KArgs &a, const FK_CONST K
         const int b = (int)(slot / a.inl_tiles_per_item);
         first = (uint32_t)b * a.inl_tiles_per_item;
         nslots = a.inl_tiles_per_item;
-        it = load_item(items);
-        const FK_CONST Roi16 *roi = (const FK_CONST Roi16 *)(ka->inl + 64) + b;
-        it.x = roi->x;
-        it.y = roi->y;
-        it.w = roi->w;
-        it.h = roi->h;
-        it.dst += (uint64_t)b * (uint64_t)a.inl_dst_stride;
-        if constexpr (rd_bilinear(Read::kind)) {
-            it.sx = (float)it.w / (float)it.ow;
-            it.sy = (float)it.h / (float)it.oh;
-        }
-        if ((it.x * C * Read::elem_size) % 4 != 0)
-            it.flags &= ~IF_SRC_VEC;
+        it = compact_item<Read::kind, C, Read::elem_size>(a, ka, b);
     } else {
         const int b = find_item(tb, n_items, slot);
         it = load_item(items + b);

@@ -69,7 +69,7 @@ fk_status launch_args(const fk_plan *p, const fk_launch_config &cfg, KArgs &a, u
 fk_status launch(const fk_plan *p, const fk_launch_config &cfg, void *d_table, uint32_t grid,
                  int32_t n_items, hipStream_t stream, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);
-bool compact_batch(const fk_plan *p, const fk_item *items, int32_t n);
+int compact_batch(const fk_plan *p, const fk_item *items, int32_t n);
 const void *kernel_table_upload();  // fk_table.hip
 fk_status run_fused(fk_plan *p, const fk_item *items, int32_t n, const fk_launch_config &cfg,
                     bool graph, hipStream_t stream, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);

@@ -126,22 +126,39 @@ struct RunHeader {      // per-run header read by the kernel (graph-friendly)
 // Small batches ride in the kernel arguments instead of a device table:
 //  - full:    ItemRec[inl_n] at inl[0..], uint32 tile_begin[inl_n + 1] at
 //             inl[kInlineTileBegin..] (inl_n <= kInlineItems);
-//  - compact: items sharing one frame, one output size and a constant
-//             output stride: an ItemRec template at inl[0..64) (item 0) and
-//             one Roi16 (x, y, w, h) per item at inl[64 + 8 b]
-//             (inl_n <= kCompactItems); item b owns tiles
-//             [b * inl_tiles_per_item, (b + 1) * inl_tiles_per_item).
+//  - compact: items sharing one frame geometry, one output size and a
+//             constant output stride: an ItemRec template at inl[0..64) (item
+//             0) and one record per item from inl[64] on; item b owns tiles
+//             [b * inl_tiles_per_item, (b + 1) * inl_tiles_per_item).  The
+//             record is the least that differs: CF_ROI of one frame, the ROI;
+//             CF_POINT of one frame read 1:1, its corner (every ROI has the
+//             output's size); CF_FRAME of several frames, frame and ROI.
 #ifndef FK_INLINE_BYTES
 #define FK_INLINE_BYTES 2560
 #endif
 constexpr int kInlineBytes = FK_INLINE_BYTES;
 constexpr int kInlineItems = (kInlineBytes - 4) / 68 < 32 ? (kInlineBytes - 4) / 68 : 32;
 constexpr int kInlineTileBegin = kInlineItems * 64;
-constexpr int kCompactItems = (kInlineBytes - 64) / 8;  // 312
-
 struct Roi16 {
     uint16_t x, y, w, h;
 };
+struct Point16 {
+    uint16_t x, y;
+};
+struct FrameRoi16 {
+    uint64_t src;
+    Roi16 roi;
+};
+static_assert(sizeof(Point16) == 4 && sizeof(Roi16) == 8 && sizeof(FrameRoi16) == 16 &&
+                  __builtin_offsetof(FrameRoi16, roi) == 8,
+              "the kernels read these records as dwords");
+enum : int32_t { CF_NONE = 0, CF_ROI = 1, CF_POINT = 2, CF_FRAME = 3 };
+constexpr int compact_items(int form)
+{
+    return (kInlineBytes - 64) / (form == CF_POINT ? (int)sizeof(Point16)
+                                  : form == CF_FRAME ? (int)sizeof(FrameRoi16) : (int)sizeof(Roi16));
+}
+constexpr int kCompactItems = compact_items(CF_ROI);  // 312 (624 points, 156 frames)
 
 // Stats write: a block's partial result for one channel.
 struct StatPartial {    // 16 bytes
@@ -172,7 +189,7 @@ struct KArgs {
     int32_t strict;        // compile-time tier: 1 = no contraction
     int32_t loop_count;    // compile-time loop chain: pairs to run
     int32_t inl_n;         // > 0: the run's items are in `inl`
-    int32_t inl_compact;   // 1: compact form
+    int32_t inl_compact;   // compact form: CF_*
     uint32_t inl_total_tiles;
     uint32_t inl_tiles_per_item;  // compact form
     int64_t inl_dst_stride;       // compact form: bytes between item outputs
