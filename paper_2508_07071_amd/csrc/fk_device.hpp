@@ -120,6 +120,14 @@ __device__ __forceinline__ void store_nt(gdst_t p, V v)
     __builtin_nontemporal_store(v, (FK_GLOBAL V *)p);
 }
 
+// The same for 8 or 16 bytes at element alignment.
+template <typename V>
+__device__ __forceinline__ void store_any(gdst_t p, V v)
+{
+    typedef V VA __attribute__((aligned(2)));
+    __builtin_nontemporal_store(v, (FK_GLOBAL VA *)p);
+}
+
 // Dwords of a streamed input that only a reduction reads: nontemporal
 // loads (measured on the u8 statistics of 16 4K frames: 67.5-69.0 us
 // against 75.9-76.7 us with ordinary loads).  The transform's plain read
@@ -221,7 +229,14 @@ __device__ __forceinline__ void bilinear_coord(int o, float scale, int in_size, 
 // bytes before the first, so it is used only when the frame base is dword
 // aligned, a frame row holds at least WB bytes, and either the ROI stops
 // above the frame's last row or its last window still ends inside that
-// row.  Other items, and fp16/fp32 frames, load element by element.
+// row.  Other items load element by element.
+//
+// fp16 and fp32 frames: a tap row's two neighbouring pixels (columns xs and
+// xs + 1 of the ROI) load as dwords at element alignment.  At the ROI's last
+// column the pair starts one pixel earlier and both taps are its second
+// pixel.  Needs a ROI of 2 columns and 32-bit row offsets; others load
+// element by element (4 C loads a pixel: 46 fp32 crops to 123 x 73 x 3 took
+// 21.7 us that way).
 template <int DT, int C>
 struct ReadCropResize {
     static constexpr int kind = RD_CROP_RESIZE;
@@ -323,7 +338,7 @@ struct ReadCropResize {
     {
         int y0, y1;
         bilinear_coord(oy, it.sy, it.h, y0, y1, ay);
-        const uint32_t col = (uint32_t)it.x * C;
+        const uint32_t col = (uint32_t)it.x * (C * elem_size);
         o0 = __umul24((uint32_t)(it.y + y0), (uint32_t)it.pitch) + col;
         o1 = __umul24((uint32_t)(it.y + y1), (uint32_t)it.pitch) + col;
     }
@@ -383,10 +398,45 @@ struct ReadCropResize {
         }
     }
 
-    // one output pixel on its own (pixel-strided lanes); prep: 0 element
-    // loads, 1 windows, 2 windows at 32-bit offsets
+    // fp16/fp32 pairs, in a frame of 32-bit offsets
+    __device__ __forceinline__ static void pixels_pair(const ItemRec &it, const int (&oy)[kUnitPx],
+                                                       const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
+    {
+        constexpr int NW = 2 * C * elem_size / 4;
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i) {
+            uint32_t o[2], w[2][NW];
+            int x0, x1;
+            float ax, ay;
+            rows_off(it, oy[i], o[0], o[1], ay);
+            bilinear_coord(ox[i], it.sx, it.w, x0, x1, ax);
+            const bool last = x1 == x0;  // the ROI's last column
+            const uint32_t x = __umul24((uint32_t)(last ? x0 - 1 : x0), (uint32_t)(C * elem_size));
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const FK_GLOBAL u32_any *p = (const FK_GLOBAL u32_any *)((gsrc_t)it.src + (uint64_t)(o[k] + x));
+#pragma unroll
+                for (int j = 0; j < NW; ++j)
+                    w[k][j] = p[j];
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float p01 = unpack_elem<DT, NW>(w[0], C + c), p11 = unpack_elem<DT, NW>(w[1], C + c);
+                const float p00 = last ? p01 : unpack_elem<DT, NW>(w[0], c);
+                const float p10 = last ? p11 : unpack_elem<DT, NW>(w[1], c);
+                const float top = fmaf(ax, p01 - p00, p00);
+                const float bot = fmaf(ax, p11 - p10, p10);
+                r[i][c] = fmaf(ay, bot - top, top);
+            }
+        }
+    }
+
+    // prep: 0 element loads, 1 windows, 2 windows (fp16/fp32: pairs) at
+    // 32-bit offsets
     __device__ __forceinline__ static int px_prep(const ItemRec &it)
     {
+        if constexpr (DT != DT_U8)
+            return it.w >= 2 && (it.flags & IF_SMALL_FRAME) ? 2 : 0;
         return !window_ok(it) ? 0 : (it.flags & IF_SMALL_FRAME) ? 2 : 1;
     }
     __device__ __forceinline__ static void load_pxs(const ItemRec &it, int prep, const int (&oy)[kUnitPx],
@@ -407,6 +457,9 @@ struct ReadCropResize {
                 }
                 return;
             }
+        } else if (prep == 2) {
+            pixels_pair(it, oy, ox, r);
+            return;
         }
 #pragma unroll
         for (int i = 0; i < kUnitPx; ++i) {
@@ -1208,9 +1261,12 @@ struct WritePlanar {
     }
 };
 
-// Packed write.  A wave whose 64 units are all whole and contiguous stages
-// its output through LDS so that each global store instruction writes one
-// contiguous run (16 bytes per lane); otherwise per-element stores.
+// Packed write.  A wave whose 64 units are all whole stages its output
+// through LDS so that each global store instruction writes one contiguous run
+// (16 bytes per lane, at the output's element alignment: items of odd size
+// follow each other in one tensor at any alignment, and 21 u8 frames of 1866 x
+// 363 x 3 into packed fp16 took 104 us with element stores); otherwise
+// per-element stores.
 template <int DT, int C>
 struct WritePacked {
     static constexpr int layout = LY_PACKED;
@@ -1254,9 +1310,9 @@ struct WritePacked {
             pack(r, w);
             if constexpr (!kStage) {
                 if constexpr (UB == 16)
-                    store_nt(dst, ux4{w[0], w[1], w[2], w[3]});
+                    store_any(dst, ux4{w[0], w[1], w[2], w[3]});
                 else
-                    store_nt(dst, ux2{w[0], w[1]});
+                    store_any(dst, ux2{w[0], w[1]});
             } else {
                 const int lane = threadIdx.x & (kWave - 1);
                 // lane's unit -> LDS, then 64 * UB bytes out in contiguous chunks
@@ -1274,9 +1330,9 @@ struct WritePacked {
                     const int ch = k * kWave + lane;
                     if (NCH % kWave == 0 || ch < NCH) {
                         if constexpr (CH == 16)
-                            store_nt(wdst + ch * 16, *(const ux4 *)(wave_lds + ch * 16));
+                            store_any(wdst + ch * 16, *(const ux4 *)(wave_lds + ch * 16));
                         else
-                            store_nt(wdst + ch * 8, *(const ux2 *)(wave_lds + ch * 8));
+                            store_any(wdst + ch * 8, *(const ux2 *)(wave_lds + ch * 8));
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1568,8 +1624,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 
 #pragma unroll
             for (int j = 0; j < G; ++j) {
-                const bool whole = nv[j] == kUnitPx && (it.flags & IF_DST_VEC);
-                const bool wave_whole = __all(whole ? 1 : 0);
+                // whole units all: consecutive in the output, whatever its rows
+                const bool wave_whole = __all(nv[j] == kUnitPx ? 1 : 0);
                 if (nv[j] > 0)
                     Write::store(it, oy[j], ox0[j], nv[j], v[j], wave_lds, wave_whole);
             }
@@ -1578,8 +1634,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 }
 
 // ----------------------------------------- gathers, pixel-strided lanes --
-// The transform pattern for a gathering read (bilinear or nearest crop+
-// resize, NV12) with a planar write, laid out for the gather: lane t of a
+// The transform pattern for a bilinear read, laid out for the gather: lane t of a
 // tile takes output pixels
 // pbase + q * T + t (q < 4K) instead of K units of 4 adjacent pixels.  Each
 // gather instruction of a wave then reads the taps of 64 consecutive output
@@ -1604,11 +1659,41 @@ __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint3
     }
 }
 
-// The chain on 4 gathered pixels per lane (v), then their planar stores;
-// p[i] = kNoPixel marks a lane's pixel outside the tile.
+// Store pixel p's C channels to its packed output position: one store of the
+// pixel (consecutive across the wave), at element alignment.
+template <int DO, int C>
+__device__ __forceinline__ void store_packed_px(gdst_t dst, uint32_t p, const float (&v)[C])
+{
+    typedef float fxc __attribute__((ext_vector_type(C), aligned(4)));
+    typedef uint32_t uxh __attribute__((ext_vector_type((C + 1) / 2), aligned(2)));
+    gdst_t q = dst + (uint64_t)p * (uint64_t)(C * DSize<DO>::v);
+    if constexpr (DO == DT_F32) {
+        fxc t;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            t[c] = v[c];
+        __builtin_nontemporal_store(t, (FK_GLOBAL fxc *)q);
+    } else {
+        uint16_t h[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            h[c] = __builtin_bit_cast(uint16_t, (_Float16)v[c]);
+        const uint32_t lo = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+        if constexpr (C == 4) {
+            __builtin_nontemporal_store(uxh{lo, (uint32_t)h[2] | ((uint32_t)h[3] << 16)}, (FK_GLOBAL uxh *)q);
+        } else {
+            typedef uint32_t u32_half __attribute__((aligned(2)));
+            __builtin_nontemporal_store((u32_half)lo, (FK_GLOBAL u32_half *)q);
+            store_elem<DT_F16>(q + 4, v[C - 1]);
+        }
+    }
+}
+
+// The chain on 4 gathered pixels per lane (v), then their stores; p[i] =
+// kNoPixel marks a lane's pixel outside the tile.
 constexpr uint32_t kNoPixel = 0xffffffffu;
 
-template <class Compute, int DO, int C>
+template <class Compute, int DO, int C, bool Packed = false>
 __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it, float (&v)[1][kUnitPx][C],
                                                const uint32_t (&p)[kUnitPx])
 {
@@ -1629,8 +1714,12 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
     const int64_t plane = (int64_t)it.ow * it.oh;
 #pragma unroll
     for (int i = 0; i < kUnitPx; ++i)
-        if (p[i] != kNoPixel)
-            store_planar_px<DO, C>((gdst_t)it.dst, plane, p[i], v[0][i]);
+        if (p[i] != kNoPixel) {
+            if constexpr (Packed)
+                store_packed_px<DO, C>((gdst_t)it.dst, p[i], v[0][i]);
+            else
+                store_planar_px<DO, C>((gdst_t)it.dst, plane, p[i], v[0][i]);
+        }
 }
 
 // One tile of pixel-strided lanes: output pixels [pbase, pbase + 4 T K)
@@ -1643,7 +1732,7 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
 // row steps, taps at 32-bit offsets from the frame base, byte positions that
 // do not depend on the clamp, and the division by reciprocal it takes 94 us;
 // 256 NV12 crops 15.5 -> 12.8 us.
-template <class Read, class Compute, int DO, int C, int K>
+template <class Read, class Compute, int DO, int C, int K, bool Packed = false>
 __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint32_t ubase, int T, int tid)
 {
     const uint32_t ow = (uint32_t)it.ow;
@@ -1677,11 +1766,11 @@ __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint3
             }
         }
         Read::load_pxs(it, prep, oy, ox, v[0]);
-        chain_store_px<Compute, DO, C>(a, it, v, p);
+        chain_store_px<Compute, DO, C, Packed>(a, it, v, p);
     }
 }
 
-template <class Read, class Compute, int DO, int C, int K>
+template <class Read, class Compute, int DO, int C, int K, bool Packed = false>
 __global__ __launch_bounds__(kMaxBlock) void k_resize_px(const KArgs a)
 {
     const FK_CONST KArgs *ka = (const FK_CONST KArgs *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1700,7 +1789,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_px(const KArgs a)
         ItemRec it;
         uint32_t ubase;
         tile_item<Read, C>(a, ka, compact, tb, items, n_items, tile, total, tile_units, it, ubase);
-        px_tile<Read, Compute, DO, C, K>(a, it, ubase, T, tid);
+        px_tile<Read, Compute, DO, C, K, Packed>(a, it, ubase, T, tid);
     }
 }
 

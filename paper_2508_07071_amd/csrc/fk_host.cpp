@@ -259,12 +259,12 @@ const void *fk::plan_kernel(const fk_plan *p, const fk_launch_config &cfg, bool 
         return kernel_muladd_loop(p->chain.read.in_dtype, p->chain.read.channels, cfg.coarsen,
                                   p->opts.strict_fp);
     default: {
-        // bilinear reads with a planar write take pixel-strided lanes on
-        // large launches, as the normalise kernel does (256 NV12 crops:
-        // 33.0 vs 35.5 us; nearest and 1:1 NV12 reads gained nothing)
+        // bilinear reads take pixel-strided lanes on large launches, as the
+        // normalise kernel does (256 NV12 crops: 33.0 vs 35.5 us; nearest and
+        // 1:1 NV12 reads gained nothing)
         int layout = p->chain.write.layout;
-        if (large && layout == FK_PLANAR && rd_bilinear(p->chain.read.kind))
-            layout = LY_PLANAR_PX;
+        if (large && rd_bilinear(p->chain.read.kind))
+            layout = layout == FK_PLANAR ? LY_PLANAR_PX : LY_PACKED_PX;
         return kernel_runtime(p->chain.read.kind, p->chain.read.in_dtype, p->chain.read.channels,
                               p->chain.write.out_dtype, layout, cfg.coarsen);
     }
@@ -542,8 +542,6 @@ uint32_t fk::build_items(const fk_plan *p, const fk_item *items, int32_t n,
             (int64_t)r.ow * r.oh < ((int64_t)1 << 31))
             flags |= IF_CONTIG;
         const bool one_row = one_row_units && (flags & IF_CONTIG);
-        if ((one_row || r.ow % kUnitPx == 0) && (uintptr_t)it.dst % 16 == 0)
-            flags |= IF_DST_VEC;
         r.flags = flags;
         tb[b] = (uint32_t)tiles;
         const uint64_t units = one_row ? ((uint64_t)r.ow * (uint64_t)r.oh + kUnitPx - 1) / kUnitPx
@@ -607,8 +605,8 @@ fk_status fk::launch_args(const fk_plan *p, const fk_launch_config &cfg, KArgs &
                           int32_t n_items, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
     // output pixels the launch covers: grid blocks of T * K units of 4 pixels
-    const bool large = (uint64_t)grid * (uint64_t)cfg.block_threads * (uint64_t)cfg.coarsen * kUnitPx >=
-                       kStridedMinPixels;
+    const uint64_t px = (uint64_t)grid * (uint64_t)cfg.block_threads * (uint64_t)cfg.coarsen * kUnitPx;
+    const bool large = px >= (p->chain.read.in_dtype == FK_U8 ? kStridedMinPixels : kStridedMinPixelsWide);
     const void *fn = plan_kernel(p, cfg, large);
     if (!fn)
         return set_error(FK_ERR_UNSUPPORTED, "no kernel for coarsening %d", cfg.coarsen);
@@ -681,18 +679,14 @@ static fk_status launch_compact(const fk_plan *p, int form, const fk_item *items
     a.inl_tiles_per_item = build_items(p, items, 1, cfg, &t, tb, batch_n);
     a.inl_total_tiles = a.inl_tiles_per_item * (uint32_t)n;
     a.inl_dst_stride = (int64_t)stride;
-    // template flags: frame base and pitch dword-aligned; outputs aligned
-    // for every item (base and stride multiples of 16); contiguous as item 0
-    // is (every item then spans the frame's whole rows)
-    const bool one_row = (t.flags & IF_CONTIG) != 0;
-    t.flags = one_row ? (int32_t)IF_CONTIG : 0;
+    // template flags: frame base and pitch dword-aligned; contiguous as item
+    // 0 is (every item then spans the frame's whole rows)
+    t.flags &= IF_CONTIG;
     uintptr_t bases = 0;
     for (int32_t b = 0; b < (form == CF_FRAME ? n : 1); ++b)
         bases |= (uintptr_t)items[b].src.ptr;
     if (bases % 4 == 0 && items[0].src.pitch_bytes % 4 == 0)
         t.flags |= IF_SRC_VEC;
-    if ((one_row || t.ow % kUnitPx == 0) && (uintptr_t)items[0].dst % 16 == 0 && a.inl_dst_stride % 16 == 0)
-        t.flags |= IF_DST_VEC;
     if (small_frame(items[0].src))
         t.flags |= IF_SMALL_FRAME;
     for (int32_t b = 0; b < n; ++b) {

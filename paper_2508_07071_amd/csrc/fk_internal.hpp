@@ -21,9 +21,9 @@ constexpr bool rd_resizes(int rk) { return rk == RD_CROP_RESIZE || rk == RD_CROP
 constexpr bool rd_bilinear(int rk) { return rk == RD_CROP_RESIZE || rk == RD_NV12_RESIZE; }
 enum : int32_t { DT_U8 = 0, DT_F16 = 1, DT_F32 = 2, DT_F64 = 3 };
 enum : int32_t { LY_PACKED = 0, LY_PLANAR = 1, LY_STATS = 2 };
-// Kernel selection only: a planar write from pixel-strided lanes (bilinear
-// reads on launches of at least kStridedMinPixels output pixels).
-enum : int32_t { LY_PLANAR_PX = 3 };
+// Kernel selection only: a planar or packed write from pixel-strided lanes
+// (bilinear reads on launches of at least kStridedMinPixels output pixels).
+enum : int32_t { LY_PLANAR_PX = 3, LY_PACKED_PX = 4 };
 
 // Normalised compute op codes.  SUB becomes ADD of the negated constant
 // (IEEE x - y is x + (-y)), CVT disappears (fp32 from the read on), swaps
@@ -97,8 +97,6 @@ static_assert(sizeof(DivRec32) == 64 && sizeof(DivRec64) == 112, "division recor
 // Item flags.
 enum : int32_t {
     IF_SRC_VEC = 1,     // source rows 4-byte aligned: unit loads as dwords
-    IF_DST_VEC = 2,     // output 16-byte aligned, its rows (IF_CONTIG: its pixels, but
-                        // for the last ones) whole units
     IF_CONTIG = 4,      // plain read of whole frame rows stored back to back, under
                         // 2^31 pixels: one row of ow * oh pixels, unit u starting
                         // u * 4 pixels after row y
@@ -215,6 +213,10 @@ const void *kernel_runtime(int read_kind, int in_dt, int channels, int out_dt, i
 // output pixels), else 4-pixel units
 const void *kernel_normalize(int coarsen, int strict, int strided);
 constexpr uint64_t kStridedMinPixels = 1u << 20;
+// The same for fp16 and fp32 frames, whose 4-pixel units hold up to 64 loaded
+// dwords a lane (15 fp32 crops to 213 x 273 x 4: 21.5 us in units, 10.6 from
+// strided lanes; 2 fp16 crops to 256 x 256 x 4 7.4 and 6.9; level at 2^17).
+constexpr uint64_t kStridedMinPixelsWide = 1u << 18;
 // crop+resize of a u8 frame with the tapped rows staged in LDS
 const void *kernel_normalize_lds(int coarsen, int strict);
 // LDS of a staged-row gather block of T threads (dynamic shared memory)

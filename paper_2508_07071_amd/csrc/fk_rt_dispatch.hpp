@@ -9,8 +9,8 @@
 namespace fk {
 
 // Read: the read op as a template of the channel count.  Strided: the read
-// also has the pixel-strided planar kernel (bilinear gathers, selected with
-// LY_PLANAR_PX).  Channels: a bit mask of the channel counts built (bit c
+// also has the pixel-strided kernels (bilinear gathers, selected with
+// LY_PLANAR_PX and LY_PACKED_PX).  Channels: a bit mask of the channel counts built (bit c
 // for c channels).
 template <template <int> class Read, bool Strided, int Channels>
 struct RuntimeTable {
@@ -19,6 +19,8 @@ struct RuntimeTable {
     {
         if constexpr (LY == LY_PLANAR_PX)
             return (const void *)&k_resize_px<Read<C>, RuntimeCompute, DO, C, K>;
+        else if constexpr (LY == LY_PACKED_PX)
+            return (const void *)&k_resize_px<Read<C>, RuntimeCompute, DO, C, K, true>;
         else if constexpr (LY == LY_PLANAR)
             return (const void *)&k_transform<Read<C>, RuntimeCompute, WritePlanar<DO, C>, C, K>;
         else
@@ -41,13 +43,18 @@ struct RuntimeTable {
     static const void *by_layout(int ly, int k)
     {
         if constexpr (Strided) {
-            if (ly == LY_PLANAR_PX)
+            // one channel: packed and planar are the same bytes
+            if (ly == LY_PLANAR_PX || (C == 1 && ly == LY_PACKED_PX))
                 return by_coarsening<C, DO, LY_PLANAR_PX>(k);
+            if constexpr (C > 1) {
+                if (ly == LY_PACKED_PX)
+                    return by_coarsening<C, DO, LY_PACKED_PX>(k);
+            }
         }
         // a read without the strided kernel takes the 4-pixel-unit planar one
         if (ly == LY_PLANAR || ly == LY_PLANAR_PX)
             return by_coarsening<C, DO, LY_PLANAR>(k);
-        return ly == LY_PACKED ? by_coarsening<C, DO, LY_PACKED>(k) : nullptr;
+        return ly == LY_PACKED || ly == LY_PACKED_PX ? by_coarsening<C, DO, LY_PACKED>(k) : nullptr;
     }
 
     template <int C>
