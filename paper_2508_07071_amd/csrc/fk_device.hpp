@@ -164,30 +164,41 @@ struct ReadPlain {
     static constexpr int kind = RD_PLAIN;
     static constexpr int dtype = DT;
     static constexpr int elem_size = DSize<DT>::v;
+    static constexpr int words = kUnitPx * C * elem_size / 4;  // dwords of a whole unit
+    __device__ __forceinline__ static gsrc_t at(const ItemRec &it, int oy, int ox0)
+    {
+        return (gsrc_t)it.src + (int64_t)(it.y + oy) * it.pitch + (int64_t)(it.x + ox0) * (C * elem_size);
+    }
+    // a whole unit as loaded, and its values
+    __device__ __forceinline__ static void fetch(const ItemRec &it, int oy, int ox0, uint32_t (&w)[words])
+    {
+        const FK_GLOBAL u32_any *p = (const FK_GLOBAL u32_any *)at(it, oy, ox0);
+#pragma unroll
+        for (int i = 0; i < words; ++i)
+            w[i] = p[i];
+    }
+    __device__ __forceinline__ static void unpack(const uint32_t (&w)[words], float (&r)[kUnitPx][C])
+    {
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                r[i][c] = unpack_elem<DT, words>(w, i * C + c);
+    }
     __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int n,
                                                 float (&r)[kUnitPx][C])
     {
-        constexpr int ES = DSize<DT>::v;
-        gsrc_t row = (gsrc_t)it.src + (int64_t)(it.y + oy) * it.pitch +
-                     (int64_t)(it.x + ox0) * (C * ES);
         if (n == kUnitPx) {
-            constexpr int NW = kUnitPx * C * ES / 4;
-            uint32_t w[NW];
-            const FK_GLOBAL u32_any *p = (const FK_GLOBAL u32_any *)row;
-#pragma unroll
-            for (int i = 0; i < NW; ++i)
-                w[i] = p[i];
-#pragma unroll
-            for (int i = 0; i < kUnitPx; ++i)
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    r[i][c] = unpack_elem<DT, NW>(w, i * C + c);
+            uint32_t w[words];
+            fetch(it, oy, ox0, w);
+            unpack(w, r);
         } else {
+            gsrc_t row = at(it, oy, ox0);
 #pragma unroll
             for (int i = 0; i < kUnitPx; ++i)
 #pragma unroll
                 for (int c = 0; c < C; ++c)
-                    r[i][c] = i < n ? load_elem<DT>(row + (i * C + c) * ES) : 0.0f;
+                    r[i][c] = i < n ? load_elem<DT>(row + (i * C + c) * elem_size) : 0.0f;
         }
     }
 };
@@ -880,23 +891,37 @@ struct OpMulAddLoop {
     __device__ __forceinline__ static void exec_tile(float (&v)[K][kUnitPx][C],
                                                      const FK_CONST float *k)
     {
-#pragma unroll 4
-        for (int p = 0; p < NPAIRS; ++p) {
-            const float m = k[S + 2 * p];
-            const float a = k[S + 2 * p + 1];
+        // four pairs' constants per fetch, the next four in flight (the table
+        // is padded by one group)
+        static_assert(NPAIRS % 4 == 0, "whole groups of pairs");
+        float q[8];
 #pragma unroll
-            for (int j = 0; j < K; ++j)
+        for (int t = 0; t < 8; ++t)
+            q[t] = k[S + t];
+#pragma unroll 1
+        for (int p = 4; p <= NPAIRS; p += 4) {
+            float nx[8];
 #pragma unroll
-                for (int i = 0; i < kUnitPx; ++i)
+            for (int t = 0; t < 8; ++t)
+                nx[t] = k[S + 2 * p + t];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        if constexpr (Strict) {
-                            const float t = v[j][i][c] * m;
-                            v[j][i][c] = t + a;
-                        } else {
-                            v[j][i][c] = fmaf(v[j][i][c], m, a);
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int i = 0; i < kUnitPx; ++i)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            if constexpr (Strict) {
+                                const float t = v[j][i][c] * q[2 * g];
+                                v[j][i][c] = t + q[2 * g + 1];
+                            } else {
+                                v[j][i][c] = fmaf(v[j][i][c], q[2 * g], q[2 * g + 1]);
+                            }
                         }
-                    }
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                q[t] = nx[t];
         }
     }
 };
@@ -955,7 +980,7 @@ template <int N, bool Strict>
 using MulAddChain = typename std::conditional<
     (N <= 16), typename MulAddSeq<Strict, std::make_index_sequence<N>>::type,
     StaticChain<OpCvtF32, OpMulAddLoop<0, N / 2, Strict>>>::type;
-static_assert(IsTileOp<OpMulAddLoop<0, 2, true>>::value && !IsTileOp<OpCvtF32>::value, "");
+static_assert(IsTileOp<OpMulAddLoop<0, 4, true>>::value && !IsTileOp<OpCvtF32>::value, "");
 
 // Compute stage over a thread's whole register tile.
 template <class Chain>
@@ -1478,7 +1503,7 @@ __device__ __forceinline__ void tile_item(const KArgs &a, const FK_CONST KArgs *
                                           uint32_t tile_units, ItemRec &it, uint32_t &ubase)
 {
     uint32_t first_tile;
-    if (compact) {
+    if (__builtin_expect(compact, 0)) {  // out of line: a batch of one starts sooner
         const int b = (int)(tile / a.inl_tiles_per_item);
         first_tile = (uint32_t)b * a.inl_tiles_per_item;
         it = compact_item<Read::kind, C, Read::elem_size>(a, ka, b);
@@ -1534,6 +1559,47 @@ constexpr int unit_group()
     return K < g ? K : g;
 }
 
+// A group's units into registers.  Reads whose units can all be loaded (those
+// past the item as its first unit) take no branch per unit, so that the loads
+// of the whole group are in flight together: gathering reads always, plain
+// reads in waves without a partial unit.  (With a branch, and a wait, per
+// unit the 256-op chain over a 4K frame, 4 units a lane, took 94 us.)
+template <class Read, int G, int C>
+__device__ __forceinline__ void load_group(const ItemRec &it, const int (&oy)[G], const int (&ox0)[G],
+                                           const int (&nv)[G], bool ragged, float (&v)[G][kUnitPx][C])
+{
+    if constexpr (rd_resizes(Read::kind)) {
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+            Read::load(it, oy[j], ox0[j], nv[j], v[j]);
+        return;
+    }
+    if constexpr (Read::kind == RD_PLAIN) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(ragged) == 0, 1)) {
+            uint32_t w[G][Read::words];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+                Read::fetch(it, oy[j], ox0[j], w[j]);
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+                Read::unpack(w[j], v[j]);
+            return;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        if (nv[j] > 0) {
+            Read::load(it, oy[j], ox0[j], nv[j], v[j]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    v[j][i][c] = 0.0f;
+        }
+    }
+}
+
 template <class Read, class Compute, class Write, int C, int K>
 __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 {
@@ -1573,12 +1639,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
         for (int g0 = 0; g0 < K; g0 += G) {
             float v[G][kUnitPx][C];
             int oy[G], ox0[G], nv[G];
+            bool ragged = false;  // a partial unit, or none where the row holds no whole one
 #pragma unroll
             for (int j = 0; j < G; ++j) {
                 const uint32_t u = ubase + (uint32_t)((g0 + j) * T + tid);
+                oy[j] = 0;
+                ox0[j] = 0;
+                nv[j] = 0;
                 if (u < units) {
                     if (contig) {
-                        oy[j] = 0;
                         ox0[j] = (int)(u * kUnitPx);
                     } else {
                         const uint32_t row = rowdiv(u);
@@ -1587,18 +1656,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
                     }
                     const int left = row_px - ox0[j];
                     nv[j] = left < kUnitPx ? left : kUnitPx;
-                    Read::load(it, oy[j], ox0[j], nv[j], v[j]);
-                } else {
-                    oy[j] = 0;
-                    ox0[j] = 0;
-                    nv[j] = 0;
-#pragma unroll
-                    for (int i = 0; i < kUnitPx; ++i)
-#pragma unroll
-                        for (int c = 0; c < C; ++c)
-                            v[j][i][c] = 0.0f;
                 }
+                ragged |= nv[j] == 0 ? row_px < kUnitPx : nv[j] != kUnitPx;
             }
+            load_group<Read, G, C>(it, oy, ox0, nv, ragged, v);
             if constexpr (C >= 3) {
                 // run-time tier: the chain's net channel swap, applied at the read
                 if (swap) {
@@ -1614,7 +1675,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
             }
 
             constexpr bool rt = std::is_same<Compute, RuntimeCompute>::value;
-            if constexpr (rt && Read::kind == RD_PLAIN && Read::elem_size == 4)
+            if constexpr (rt && Read::kind == RD_PLAIN)
                 own_registers(v);
 
             Compute::template apply<G, C>(a, v);

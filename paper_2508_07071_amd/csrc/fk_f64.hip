@@ -20,6 +20,48 @@ __device__ __forceinline__ double load_f64(gsrc_t p)
         return (double)load_elem<DI>(p);  // u8, fp16, fp32: exact in fp32, then in fp64
 }
 
+// The C elements of a pixel: whole dwords at element alignment where they
+// fill some, so that a lane's pixel takes one or two loads.
+template <int DI, int C>
+__device__ __forceinline__ void load_px_f64(gsrc_t p, double (&v)[C])
+{
+    constexpr int ES = DSize<DI>::v;
+    if constexpr (C > 1 && C * ES % 4 == 0) {
+        constexpr int NW = C * ES / 4;
+        uint32_t w[NW];
+        const FK_GLOBAL u32_any *q = (const FK_GLOBAL u32_any *)p;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+            w[i] = q[i];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if constexpr (DI == DT_F64)
+                v[c] = __builtin_bit_cast(double, (uint64_t)w[2 * c] | ((uint64_t)w[2 * c + 1] << 32));
+            else
+                v[c] = (double)unpack_elem<DI, NW>(w, c);
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            v[c] = load_f64<DI>(p + c * ES);
+    }
+}
+
+// A packed pixel's doubles as 16-byte stores (and one of 8): stores of one
+// channel each left every line to several partial writes (a u8 frame of 2750 x
+// 1598 x 3 through one op into packed fp64).
+template <int C>
+__device__ __forceinline__ void store_px_f64(FK_GLOBAL double *q, const double (&v)[C])
+{
+    typedef double dx2 __attribute__((ext_vector_type(2)));
+    typedef dx2 dx2_any __attribute__((aligned(8)));
+#pragma unroll
+    for (int c = 0; c + 1 < C; c += 2)
+        __builtin_nontemporal_store(dx2{v[c], v[c + 1]}, (FK_GLOBAL dx2_any *)(q + c));
+    if constexpr (C % 2)
+        __builtin_nontemporal_store(v[C - 1], q + C - 1);
+}
+
 // tile_item's view of the read: a plain read of DI elements
 template <int DI>
 struct ReadPlainF64 {
@@ -68,9 +110,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_f64(const KArgs a)
                     const uint32_t row = rowdiv(p);
                     const uint32_t col = p - row * (uint32_t)it.ow;
                     gsrc_t s = roi + (int64_t)row * it.pitch + (int64_t)col * (C * ES);
-#pragma unroll
-                    for (int c = 0; c < C; ++c)
-                        v[0][i][c] = load_f64<DI>(s + c * ES);
+                    load_px_f64<DI, C>(s, v[0][i]);
                 } else {
 #pragma unroll
                     for (int c = 0; c < C; ++c)
@@ -92,11 +132,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_f64(const KArgs a)
             for (int i = 0; i < P; ++i) {
                 const uint32_t p = pbase + (uint32_t)((q0 + i) * T + tid);
                 if (p < npx) {
+                    if constexpr (Planar) {
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        // planar: plane c; packed: channel c of the pixel
-                        const int64_t o = Planar ? (int64_t)c * npx + p : (int64_t)p * C + c;
-                        __builtin_nontemporal_store(v[0][i][c], dst + o);
+                        for (int c = 0; c < C; ++c)
+                            __builtin_nontemporal_store(v[0][i][c], dst + (int64_t)c * npx + p);
+                    } else {
+                        store_px_f64<C>(dst + (int64_t)p * C, v[0][i]);
                     }
                 }
             }

@@ -386,6 +386,8 @@ extern "C" fk_status fk_plan_create(const fk_chain_desc *chain, int32_t max_batc
             consts.resize((kDivRecOffset + sizeof q) / sizeof(float), 0.0f);
             std::memcpy((char *)consts.data() + kDivRecOffset, &q, sizeof q);
         }
+        if (p->family == FAM_MULADD)
+            consts.resize(consts.size() + 8, 0.0f);  // the kernels fetch one group ahead
         normalise_chain(&p->chain, o.strict_fp != 0, p->ops, p->swap);
         p->cfg = o.config_source == FK_CONFIG_MANUAL ? o.manual : default_config(p);
         if (!runs_op_list(p)) {
