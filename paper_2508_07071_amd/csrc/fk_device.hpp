@@ -1400,6 +1400,7 @@ __device__ __forceinline__ ItemRec load_item(const FK_CONST ItemRec *p)
 struct RowDiv {
     uint32_t upr;
     double rcp;
+    __device__ __forceinline__ RowDiv() : upr(1), rcp(1.0) {}  // never asked
     __device__ __forceinline__ explicit RowDiv(uint32_t d) : upr(d), rcp(1.0 / (double)d) {}
     __device__ __forceinline__ uint32_t operator()(uint32_t u) const
     {
@@ -1503,11 +1504,18 @@ __device__ __forceinline__ void tile_item(const KArgs &a, const FK_CONST KArgs *
                                           uint32_t tile_units, ItemRec &it, uint32_t &ubase)
 {
     uint32_t first_tile;
-    if (__builtin_expect(compact, 0)) {  // out of line: a batch of one starts sooner
-        const int b = (int)(tile / a.inl_tiles_per_item);
-        first_tile = (uint32_t)b * a.inl_tiles_per_item;
+    if (__builtin_expect(a.inl_n == 1, 1)) {
+        // one item in the kernel arguments: no lookup before its record
+        first_tile = 0;
+        it = load_item((const FK_CONST ItemRec *)ka->inl);
+    } else if (compact) {
+        uint32_t per_item = a.inl_tiles_per_item;
+        asm volatile("" : "+s"(per_item));  // divide here, not ahead of the branches
+        const int b = (int)(tile / per_item);
+        first_tile = (uint32_t)b * per_item;
         it = compact_item<Read::kind, C, Read::elem_size>(a, ka, b);
     } else {
+        asm volatile("" : "+s"(total));
         const int b = find_item_guess(tb, n_items, tile, total);
         it = load_item(items + b);
         first_tile = tb[b];
@@ -1633,7 +1641,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
         const int row_px = contig ? it.ow * it.oh : it.ow;
         const uint32_t upr = (uint32_t)(row_px + kUnitPx - 1) / kUnitPx;
         const uint32_t units = contig ? upr : upr * (uint32_t)it.oh;
-        const RowDiv rowdiv(upr);
+        const RowDiv rowdiv = contig ? RowDiv() : RowDiv(upr);
         constexpr int G = unit_group<Read, Compute, Write, C, K>();
 #pragma unroll 1
         for (int g0 = 0; g0 < K; g0 += G) {
