@@ -133,7 +133,7 @@ __device__ __forceinline__ void store_any(gdst_t p, V v)
 // against 75.9-76.7 us with ordinary loads).  The transform's plain read
 // keeps ordinary loads: on frames already in the Infinity Cache they hit
 // there (18.9 us against 22.2 us per 4K launch), from HBM the two are even.
-__device__ __forceinline__ uint32_t load_stream(const FK_GLOBAL uint32_t *p)
+__device__ __forceinline__ uint32_t load_stream(const FK_GLOBAL u32_any *p)
 {
     return __builtin_nontemporal_load(p);
 }
@@ -2168,7 +2168,7 @@ __device__ __forceinline__ void block_reduce(StatAcc<C> &acc, StatPartial (*lds)
     __syncthreads();
 }
 
-// One tile of a plain read whose units are all whole and dword-aligned:
+// One tile of a plain read's whole units (at any alignment):
 // a group of the K units' raw dwords is fetched first (GW loads in flight
 // per lane), then each unit is unpacked, run through the ops and
 // accumulated.  All K units form one group while their words fit in 48
@@ -2189,7 +2189,7 @@ constexpr int stats_group()
 }
 
 template <class Read, class Compute, int C, int K>
-__device__ __forceinline__ void stats_tile_vec(const KArgs &a, const ItemRec &it, uint32_t ubase,
+__device__ __forceinline__ void stats_tile_vec(const KArgs &a, const ItemRec &it, bool contig, uint32_t ubase,
                                                uint32_t units, const RowDiv &rowdiv, int T, int tid,
                                                bool swap, StatAcc<C> &acc)
 {
@@ -2205,14 +2205,12 @@ __device__ __forceinline__ void stats_tile_vec(const KArgs &a, const ItemRec &it
             const uint32_t u = ubase + (uint32_t)((g0 + j) * T + tid);
             ok[j] = u < units;
             if (ok[j]) {
-                const uint32_t row = rowdiv(u);
-                const int ox0 = (int)(u - row * rowdiv.upr) * kUnitPx;
-                const FK_GLOBAL uint32_t *p =
-                    (const FK_GLOBAL uint32_t *)((gsrc_t)it.src + (int64_t)(it.y + (int)row) * it.pitch +
-                                                 (int64_t)(it.x + ox0) * (C * DSize<DT>::v));
-#pragma unroll
-                for (int i = 0; i < NW; ++i)
-                    w[j][i] = p[i];
+                uint32_t row = 0, col = u;
+                if (!contig) {
+                    row = rowdiv(u);
+                    col = u - row * rowdiv.upr;
+                }
+                Read::fetch(it, (int)row, (int)(col * kUnitPx), w[j]);
             }
         }
 #pragma unroll
@@ -2341,7 +2339,7 @@ constexpr bool plain_u8()
         return false;
 }
 
-// Fetch one tile of u8 units (whole and dword-aligned) for the integer
+// Fetch one tile of whole u8 units (at any alignment) for the integer
 // statistics.  Lanes past the item's last unit load its last unit instead
 // and are masked out (ok = false): every lane issues the same loads, so the
 // wait for this tile counts exactly the loads issued after it.
@@ -2365,7 +2363,7 @@ __device__ __forceinline__ void fetch_tile_u8(const ItemRec &it, uint32_t ubase,
             const int ox0 = (int)(u - row * rowdiv.upr) * kUnitPx;
             q = base + (int64_t)row * it.pitch + (int64_t)(it.x + ox0) * C;
         }
-        const FK_GLOBAL uint32_t *p = (const FK_GLOBAL uint32_t *)q;
+        const FK_GLOBAL u32_any *p = (const FK_GLOBAL u32_any *)q;
 #pragma unroll
         for (int i = 0; i < C; ++i)
             w[j][i] = load_stream(p + i);
@@ -2410,6 +2408,22 @@ __device__ __forceinline__ void stats_store_partial(const KArgs &a, StatAcc<C> &
     __syncthreads();  // `red` is reused by the next slot
 }
 
+// A plain read's item as whole units and what they leave over: a contiguous
+// item is one row, so at most 3 pixels of it are left; other items leave up
+// to 3 a row, which the item's threads take a row each.  (Items of odd width
+// or alignment went value by value: 54 u8 frames of 101 x 1155 x 4 took 30 us.)
+struct StatRows {
+    bool contig;
+    int rows, whole, tail;  // rows, whole units and left-over pixels of each
+    __device__ __forceinline__ explicit StatRows(const ItemRec &it) : contig(it.flags & IF_CONTIG)
+    {
+        const int px = contig ? it.ow * it.oh : it.ow;
+        rows = contig ? 1 : it.oh;
+        whole = px / kUnitPx;
+        tail = px % kUnitPx;
+    }
+};
+
 template <class Read, class Compute, int C, int K>
 __global__ __launch_bounds__(kMaxBlock) void k_stats(const KArgs a)
 {
@@ -2431,36 +2445,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_stats(const KArgs a)
         ItemRec it;
         uint32_t first, nslots;
         stats_slot_item<Read, C>(a, ka, compact, tb, items, n_items, slot, it, first, nslots);
-        const uint32_t upr = (uint32_t)(it.ow + kUnitPx - 1) / kUnitPx;
-        const uint32_t units = upr * (uint32_t)it.oh;
-        const uint32_t item_tiles = (units + tile_units - 1) / tile_units;
-        const RowDiv rowdiv(upr);
-
         StatAcc<C> acc;
         acc.init();
-        // the K units of a thread run one at a time (read, ops, accumulate):
-        // only one unit's values are live, whatever K
-        for (uint32_t t = slot - first; t < item_tiles; t += nslots) {
-            const uint32_t ubase = t * tile_units;
-            if constexpr (Read::kind == RD_PLAIN) {
-                // whole dword-aligned units everywhere in the item: a flag of
-                // the item, so the branch is uniform
-                if ((it.flags & IF_SRC_VEC) && it.ow % kUnitPx == 0) {
-                    stats_tile_vec<Read, Compute, C, K>(a, it, ubase, units, rowdiv, T, tid, swap, acc);
-                    continue;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const uint32_t u = ubase + (uint32_t)(j * T + tid);
-                if (u >= units)
-                    continue;
-                const uint32_t row = rowdiv(u);
-                const int ox0 = (int)(u - row * upr) * kUnitPx;
-                const int left = it.ow - ox0;
-                const int nv = left < kUnitPx ? left : kUnitPx;
+        auto unit = [&](int row, int ox0, int nv) {
                 float v[1][kUnitPx][C];
-                Read::load(it, (int)row, ox0, nv, v[0]);
+                Read::load(it, row, ox0, nv, v[0]);
                 if constexpr (C >= 3) {
                     if (swap) {
 #pragma unroll
@@ -2482,6 +2471,37 @@ __global__ __launch_bounds__(kMaxBlock) void k_stats(const KArgs a)
                             acc.sum[c] += (double)v[0][i][c];
                         }
                     }
+        };
+        // the K units of a thread run one at a time (read, ops, accumulate):
+        // only one unit's values are live, whatever K
+        if constexpr (Read::kind == RD_PLAIN) {
+            const StatRows g(it);
+            const uint32_t units = (uint32_t)g.whole * (uint32_t)g.rows;
+            const uint32_t item_tiles = (units + tile_units - 1) / tile_units;
+            const RowDiv rowdiv = g.contig || g.whole == 0 ? RowDiv() : RowDiv((uint32_t)g.whole);
+            for (uint32_t t = slot - first; t < item_tiles; t += nslots)
+                stats_tile_vec<Read, Compute, C, K>(a, it, g.contig, t * tile_units, units, rowdiv, T, tid, swap,
+                                                    acc);
+            if (g.tail)
+                for (uint32_t r = (slot - first) * (uint32_t)T + (uint32_t)tid; r < (uint32_t)g.rows;
+                     r += nslots * (uint32_t)T)
+                    unit((int)r, g.whole * kUnitPx, g.tail);
+        } else {
+            const uint32_t upr = (uint32_t)(it.ow + kUnitPx - 1) / kUnitPx;
+            const uint32_t units = upr * (uint32_t)it.oh;
+            const uint32_t item_tiles = (units + tile_units - 1) / tile_units;
+            const RowDiv rowdiv(upr);
+            for (uint32_t t = slot - first; t < item_tiles; t += nslots) {
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const uint32_t u = t * tile_units + (uint32_t)(j * T + tid);
+                    if (u >= units)
+                        continue;
+                    const uint32_t row = rowdiv(u);
+                    const int ox0 = (int)(u - row * upr) * kUnitPx;
+                    const int left = it.ow - ox0;
+                    unit((int)row, ox0, left < kUnitPx ? left : kUnitPx);
+                }
             }
         }
         stats_store_partial<C>(a, acc, red, slot, tid, T);
@@ -2491,8 +2511,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_stats(const KArgs a)
 // The stats write of a u8 plain read with no arithmetic after the cast:
 // the same slots, tiles and partials as k_stats, with integer accumulation
 // (U8Acc).  A kernel of its own, so that it keeps fewer registers live than
-// the float path and more waves stay resident.  Items whose units are not
-// all whole and dword-aligned take a byte-by-byte loop.
+// the float path and more waves stay resident.
 template <int C, int K>
 __global__ __launch_bounds__(kMaxBlock) void k_stats_u8(const KArgs a)
 {
@@ -2515,66 +2534,67 @@ __global__ __launch_bounds__(kMaxBlock) void k_stats_u8(const KArgs a)
         ItemRec it;
         uint32_t first, nslots;
         stats_slot_item<Read, C>(a, ka, compact, tb, items, n_items, slot, it, first, nslots);
-        const uint32_t upr = (uint32_t)(it.ow + kUnitPx - 1) / kUnitPx;
-        const uint32_t units = upr * (uint32_t)it.oh;
+        const StatRows g(it);
+        const uint32_t units = (uint32_t)g.whole * (uint32_t)g.rows;
         const uint32_t item_tiles = (units + tile_units - 1) / tile_units;
-        const RowDiv rowdiv(upr);
+        const RowDiv rowdiv = g.contig || g.whole == 0 ? RowDiv() : RowDiv((uint32_t)g.whole);
 
         StatAcc<C> acc;
         acc.init();
-        if ((it.flags & IF_SRC_VEC) && it.ow % kUnitPx == 0) {
-            // software pipeline over two register buffers: tile t + nslots
-            // is in flight while tile t is accumulated
+        if (slot - first < item_tiles) {
+            // software pipeline over two register buffers of KG units a lane:
+            // the next group is in flight while one is accumulated.  A group
+            // is a tile, or half of one where two tiles of 8 units of 4
+            // channels would not leave a register.
+            constexpr int KG = C == 4 && K == 8 ? 4 : K, NG = K / KG;
             U8Acc<C> iacc;
             iacc.init();
-            uint32_t wa[K][C], wb[K][C];
-            bool oka[K], okb[K];
-            uint32_t t = slot - first;
-            fetch_tile_u8<C, K>(it, t * tile_units, units, rowdiv, T, tid, wa, oka);
+            uint32_t wa[KG][C], wb[KG][C];
+            bool oka[KG], okb[KG];
+            uint32_t t = slot - first, sub = 0;
+            auto fetch = [&](uint32_t (&w)[KG][C], bool (&ok)[KG]) {
+                fetch_tile_u8<C, KG>(it, t * tile_units + sub * (uint32_t)(T * KG), units, rowdiv, T, tid, w, ok);
+            };
+            auto next = [&]() {  // false past the item's last group
+                if (++sub == NG) {
+                    sub = 0;
+                    t += nslots;
+                }
+                return t < item_tiles;
+            };
+            fetch(wa, oka);
             for (;;) {
-                const uint32_t t1 = t + nslots;
-                if (t1 >= item_tiles) {
+                if (!next()) {
                     iacc.add_tile(wa, oka);
                     break;
                 }
-                fetch_tile_u8<C, K>(it, t1 * tile_units, units, rowdiv, T, tid, wb, okb);
+                fetch(wb, okb);
                 iacc.add_tile(wa, oka);
                 iacc.flush_sums(acc);
-                const uint32_t t2 = t1 + nslots;
-                if (t2 >= item_tiles) {
+                if (!next()) {
                     iacc.add_tile(wb, okb);
                     break;
                 }
-                fetch_tile_u8<C, K>(it, t2 * tile_units, units, rowdiv, T, tid, wa, oka);
+                fetch(wa, oka);
                 iacc.add_tile(wb, okb);
                 iacc.flush_sums(acc);
-                t = t2;
             }
             iacc.flush_sums(acc);  // at most 2 * K * 4 * 255 per channel between flushes
             iacc.merge_minmax(acc);
-        } else {
-            for (uint32_t t = slot - first; t < item_tiles; t += nslots) {
-                for (int j = 0; j < K; ++j) {
-                    const uint32_t u = t * tile_units + (uint32_t)(j * T + tid);
-                    if (u >= units)
-                        break;
-                    const uint32_t row = rowdiv(u);
-                    const int ox0 = (int)(u - row * upr) * kUnitPx;
-                    const int left = it.ow - ox0;
-                    const int nv = left < kUnitPx ? left : kUnitPx;
-                    gsrc_t p = (gsrc_t)it.src + (int64_t)(it.y + (int)row) * it.pitch +
-                               (int64_t)(it.x + ox0) * C;
-                    for (int i = 0; i < nv; ++i)
-#pragma unroll
-                        for (int c = 0; c < C; ++c) {
-                            const float x = (float)p[i * C + c];
-                            acc.mn[c] = fminf(acc.mn[c], x);
-                            acc.mx[c] = fmaxf(acc.mx[c], x);
-                            acc.sum[c] += (double)x;
-                        }
-                }
-            }
         }
+        if (g.tail)
+            for (uint32_t r = (slot - first) * (uint32_t)T + (uint32_t)tid; r < (uint32_t)g.rows;
+                 r += nslots * (uint32_t)T) {
+                gsrc_t p = Read::at(it, (int)r, g.whole * kUnitPx);
+                for (int i = 0; i < g.tail; ++i)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const float x = (float)p[i * C + c];
+                        acc.mn[c] = fminf(acc.mn[c], x);
+                        acc.mx[c] = fmaxf(acc.mx[c], x);
+                        acc.sum[c] += (double)x;
+                    }
+            }
         if constexpr (C >= 3) {
             // the chain's net swap: statistics of source channel 2 are
             // those of output channel 0, and the other way round
