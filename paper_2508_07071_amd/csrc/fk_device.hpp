@@ -242,12 +242,13 @@ __device__ __forceinline__ void bilinear_coord(int o, float scale, int in_size, 
 // above the frame's last row or its last window still ends inside that
 // row.  Other items load element by element.
 //
-// fp16 and fp32 frames: a tap row's two neighbouring pixels (columns xs and
-// xs + 1 of the ROI) load as dwords at element alignment.  At the ROI's last
-// column the pair starts one pixel earlier and both taps are its second
-// pixel.  Needs a ROI of 2 columns and 32-bit row offsets; others load
-// element by element (4 C loads a pixel: 46 fp32 crops to 123 x 73 x 3 took
-// 21.7 us that way).
+// fp16 frames, and fp32 frames of one channel: a tap row's two neighbouring
+// pixels (columns xs and xs + 1 of the ROI) load as dwords at element
+// alignment.  At the ROI's last column the pair starts one pixel earlier and
+// both taps are its second pixel.  Needs a ROI of 2 columns and 32-bit row
+// offsets; others load element by element.  fp32 pixels of 3 and 4 channels
+// load on their own: the element loads of one merge into one, and pairs of 24
+// and 32 bytes took longer (17 crops to 512 x 512 x 4: 49.7 us against 37.4).
 template <int DT, int C>
 struct ReadCropResize {
     static constexpr int kind = RD_CROP_RESIZE;
@@ -446,6 +447,8 @@ struct ReadCropResize {
     // 32-bit offsets
     __device__ __forceinline__ static int px_prep(const ItemRec &it)
     {
+        if constexpr (DT == DT_F32 && C > 1)
+            return 0;
         if constexpr (DT != DT_U8)
             return it.w >= 2 && (it.flags & IF_SMALL_FRAME) ? 2 : 0;
         return !window_ok(it) ? 0 : (it.flags & IF_SMALL_FRAME) ? 2 : 1;
@@ -1550,8 +1553,8 @@ __device__ __forceinline__ void own_registers(float (&v)[G][kUnitPx][C])
 // whole tile fits, else the largest group that compiles without scratch
 // (from the kernels' scratch sizes): 4 units of 3 channels, 2 of 4; 2 for
 // the run-time op list into planar fp32 (91 registers where 4 would leave
-// four waves a SIMD), for the NV12 resize, the nearest and the fp32 resize
-// reads.
+// four waves a SIMD), for the NV12 resize and the nearest reads; 1 for the
+// fp32 resize read.
 template <class Read, class Compute, class Write, int C, int K>
 constexpr int unit_group()
 {
@@ -1562,8 +1565,8 @@ constexpr int unit_group()
         g = 2;
     if ((Read::kind == RD_NV12_RESIZE || (rt && Read::kind == RD_CROP_NEAREST)) && g > 2)
         g = 2;  // four converted taps per pixel; 64-bit source indices
-    if (rt && Read::kind == RD_CROP_RESIZE && Read::elem_size == 4 && C == 3 && g > 2)
-        g = 2;  // 12 loads in flight per pixel
+    if (rt && Read::kind == RD_CROP_RESIZE && Read::elem_size == 4 && C > 1)
+        g = 1;  // 12 or 16 loaded values per pixel
     return K < g ? K : g;
 }
 

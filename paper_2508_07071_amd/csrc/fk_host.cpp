@@ -283,8 +283,10 @@ bool fk::per_pixel(const fk_plan *p)
 
 size_t fk::lds_bytes(const fk_plan *p, const fk_launch_config &cfg)
 {
-    if (p->family == FAM_F64)
-        return 0;
+    if (p->family == FAM_F64)  // a pixel of doubles per thread, staged by packed writes
+        return p->chain.write.layout == FK_PACKED && p->chain.read.channels > 1
+                   ? (size_t)cfg.block_threads * p->chain.read.channels * sizeof(double)
+                   : 0;
     if (p->family == FAM_NORMALIZE && p->opts.gather == FK_GATHER_LDS)
         return lds_gather_bytes((uint32_t)cfg.block_threads);
     if (p->chain.write.layout != FK_PACKED || per_pixel(p))

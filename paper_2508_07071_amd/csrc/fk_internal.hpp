@@ -213,9 +213,10 @@ const void *kernel_runtime(int read_kind, int in_dt, int channels, int out_dt, i
 // output pixels), else 4-pixel units
 const void *kernel_normalize(int coarsen, int strict, int strided);
 constexpr uint64_t kStridedMinPixels = 1u << 20;
-// The same for fp16 and fp32 frames, whose 4-pixel units hold up to 64 loaded
-// dwords a lane (15 fp32 crops to 213 x 273 x 4: 21.5 us in units, 10.6 from
-// strided lanes; 2 fp16 crops to 256 x 256 x 4 7.4 and 6.9; level at 2^17).
+// The same for fp16 and fp32 frames, whose pixels hold up to 16 loaded dwords
+// a lane (units and strided lanes: 15 fp32 crops to 213 x 273 x 4 13.5 and
+// 10.1 us, 6 to 224 x 224 x 3 6.3 and 6.0, 6 fp16 ones 6.5 and 6.2; one
+// channel is level, 5.5 and 5.6 for 10 fp32 crops; at 2^17 all are level).
 constexpr uint64_t kStridedMinPixelsWide = 1u << 18;
 // crop+resize of a u8 frame with the tapped rows staged in LDS
 const void *kernel_normalize_lds(int coarsen, int strict);
