@@ -683,16 +683,19 @@ static fk_status launch_compact(const fk_plan *p, int form, const fk_item *items
     a.inl_tiles_per_item = build_items(p, items, 1, cfg, &t, tb, batch_n);
     a.inl_total_tiles = a.inl_tiles_per_item * (uint32_t)n;
     a.inl_dst_stride = (int64_t)stride;
-    // template flags: frame base and pitch dword-aligned; contiguous as item
-    // 0 is (every item then spans the frame's whole rows)
-    t.flags &= IF_CONTIG;
-    uintptr_t bases = 0;
-    for (int32_t b = 0; b < (form == CF_FRAME ? n : 1); ++b)
-        bases |= (uintptr_t)items[b].src.ptr;
-    if (bases % 4 == 0 && items[0].src.pitch_bytes % 4 == 0)
-        t.flags |= IF_SRC_VEC;
-    if (small_frame(items[0].src))
-        t.flags |= IF_SMALL_FRAME;
+    // The template's flags are item 0's: contiguous as item 0 is (every item
+    // then spans the frame's whole rows), and the frame geometry's.  Only
+    // IF_SRC_VEC differs by item: of several items it says that every frame
+    // base and the pitch are dword-aligned, and the kernels clear it by each
+    // item's column (compact_item); a single item keeps its own, since its
+    // record is taken as it stands (tile_item).
+    if (n > 1) {
+        uintptr_t bases = 0;
+        for (int32_t b = 0; b < (form == CF_FRAME ? n : 1); ++b)
+            bases |= (uintptr_t)items[b].src.ptr;
+        const bool aligned = bases % 4 == 0 && items[0].src.pitch_bytes % 4 == 0;
+        t.flags = aligned ? t.flags | IF_SRC_VEC : t.flags & ~IF_SRC_VEC;
+    }
     for (int32_t b = 0; b < n; ++b) {
         const fk_item &it = items[b];
         const Roi16 roi = {(uint16_t)it.x, (uint16_t)it.y, (uint16_t)it.w, (uint16_t)it.h};
