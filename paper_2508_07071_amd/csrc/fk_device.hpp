@@ -1581,8 +1581,18 @@ __device__ __forceinline__ void load_group(const ItemRec &it, const int (&oy)[G]
 {
     if constexpr (rd_resizes(Read::kind)) {
 #pragma unroll
-        for (int j = 0; j < G; ++j)
-            Read::load(it, oy[j], ox0[j], nv[j], v[j]);
+        for (int j = 0; j < G; ++j) {
+            // units past the item in the whole wave are not read
+            if (j == 0 || __builtin_amdgcn_ballot_w64(nv[j] > 0) != 0) {
+                Read::load(it, oy[j], ox0[j], nv[j], v[j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kUnitPx; ++i)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        v[j][i][c] = 0.0f;
+            }
+        }
         return;
     }
     if constexpr (Read::kind == RD_PLAIN) {
@@ -1670,6 +1680,9 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
                 }
                 ragged |= nv[j] == 0 ? row_px < kUnitPx : nv[j] != kUnitPx;
             }
+            // a wave past the item is done with the tile
+            if (__builtin_amdgcn_ballot_w64(nv[0] > 0) == 0)
+                break;
             load_group<Read, G, C>(it, oy, ox0, nv, ragged, v);
             if constexpr (C >= 3) {
                 // run-time tier: the chain's net channel swap, applied at the read
@@ -1818,6 +1831,10 @@ __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint3
     // groups of 4 pixels per lane, one after another: registers do not
     // grow with K (K only sizes the tile)
     for (int j = 0; j < K; ++j) {
+        // a wave past the item is done with the tile (asked between groups
+        // only: ahead of the first the branch cost 256 crops 1 %)
+        if (j > 0 && __builtin_amdgcn_ballot_w64(at < npx) == 0)
+            break;
         float v[1][kUnitPx][C];
         uint32_t p[kUnitPx];
         int oy[kUnitPx], ox[kUnitPx];

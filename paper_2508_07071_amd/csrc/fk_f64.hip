@@ -118,6 +118,9 @@ __global__ __launch_bounds__(kMaxBlock) void k_f64(const KArgs a)
         constexpr int P0 = C == 1 ? 8 : C == 3 ? 4 : 2;
         constexpr int P = P0 < 4 * K ? P0 : 4 * K;
         for (int q0 = 0; q0 < 4 * K; q0 += P) {
+            // a wave past the item is done with the tile
+            if (__builtin_amdgcn_ballot_w64(pbase + (uint32_t)(q0 * T + tid) < npx) == 0)
+                break;
             double v[1][P][C];
 #pragma unroll
             for (int i = 0; i < P; ++i) {
