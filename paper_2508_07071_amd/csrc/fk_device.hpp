@@ -550,25 +550,26 @@ struct ReadCropNearest {
         for (int c = 0; c < C; ++c)
             r[c] = load_elem<DT>(row + (sx * C + c) * ES);
     }
-    __device__ __forceinline__ static bool px_prep(const ItemRec &it) { return window_ok(it); }
-    __device__ __forceinline__ static void load_pxs(const ItemRec &it, bool win, const int (&oy)[kUnitPx],
-                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C])
-    {
-        if (win) {
-#pragma unroll
-            for (int i = 0; i < kUnitPx; ++i)
-                pixel(it, row_of(it, oy[i]), ox[i], true, r[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < kUnitPx; ++i)
-                pixel(it, row_of(it, oy[i]), ox[i], false, r[i]);
-        }
-    }
-
+    // a unit: its row once, columns past the row's end moved onto its last one
+    // (as load_unit_pxs)
     __device__ __forceinline__ static void load(const ItemRec &it, int oy, int ox0, int,
                                                 float (&r)[kUnitPx][C])
     {
-        load_unit_pxs<ReadCropNearest, C>(it, oy, ox0, r);
+        gsrc_t row = row_of(it, oy);
+        const bool win = window_ok(it);
+        int ox[kUnitPx];
+#pragma unroll
+        for (int i = 0; i < kUnitPx; ++i)
+            ox[i] = ox0 + i < it.ow ? ox0 + i : it.ow - 1;
+        if (win) {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+                pixel(it, row, ox[i], true, r[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+                pixel(it, row, ox[i], false, r[i]);
+        }
     }
 };
 
