@@ -1321,8 +1321,10 @@ struct WritePlanar {
 // through LDS so that each global store instruction writes one contiguous run
 // (16 bytes per lane, at the output's element alignment: items of odd size
 // follow each other in one tensor at any alignment, and 21 u8 frames of 1866 x
-// 363 x 3 into packed fp16 took 104 us with element stores); otherwise
-// per-element stores.
+// 363 x 3 into packed fp16 took 104 us with element stores); other waves store
+// their whole units from the lanes in 16-byte pieces (rows with a partial unit
+// in every wave: 700 fp32 frames of about 86 x 415 x 3 into packed fp32 445 us
+// with element stores, 243 so), and the partial ones value by value.
 template <int DT, int C>
 struct WritePacked {
     static constexpr int layout = LY_PACKED;
@@ -1361,39 +1363,42 @@ struct WritePacked {
     {
         const int64_t p0 = (int64_t)oy * it.ow + ox0;
         gdst_t dst = (gdst_t)it.dst + p0 * (C * ES);
-        if (all_whole) {
+        if (kStage && all_whole) {
             uint32_t w[UB / 4];
             pack(r, w);
-            if constexpr (!kStage) {
-                if constexpr (UB == 16)
-                    store_any(dst, ux4{w[0], w[1], w[2], w[3]});
-                else
-                    store_any(dst, ux2{w[0], w[1]});
-            } else {
-                const int lane = threadIdx.x & (kWave - 1);
-                // lane's unit -> LDS, then 64 * UB bytes out in contiguous chunks
-                uint32_t *mine = (uint32_t *)(wave_lds + lane * UB);
+            const int lane = threadIdx.x & (kWave - 1);
+            // lane's unit -> LDS, then 64 * UB bytes out in contiguous chunks
+            uint32_t *mine = (uint32_t *)(wave_lds + lane * UB);
 #pragma unroll
-                for (int i = 0; i < UB / 4; ++i)
-                    mine[i] = w[i];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                gdst_t wdst = dst - (int64_t)lane * UB;  // the wave's first unit
-                constexpr int NCH = kWave * UB / CH;
+            for (int i = 0; i < UB / 4; ++i)
+                mine[i] = w[i];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            gdst_t wdst = dst - (int64_t)lane * UB;  // the wave's first unit
+            constexpr int NCH = kWave * UB / CH;
 #pragma unroll
-                for (int k = 0; k < (NCH + kWave - 1) / kWave; ++k) {
-                    const int ch = k * kWave + lane;
-                    if (NCH % kWave == 0 || ch < NCH) {
-                        if constexpr (CH == 16)
-                            store_any(wdst + ch * 16, *(const ux4 *)(wave_lds + ch * 16));
-                        else
-                            store_any(wdst + ch * 8, *(const ux2 *)(wave_lds + ch * 8));
-                    }
+            for (int k = 0; k < (NCH + kWave - 1) / kWave; ++k) {
+                const int ch = k * kWave + lane;
+                if (NCH % kWave == 0 || ch < NCH) {
+                    if constexpr (CH == 16)
+                        store_any(wdst + ch * 16, *(const ux4 *)(wave_lds + ch * 16));
+                    else
+                        store_any(wdst + ch * 8, *(const ux2 *)(wave_lds + ch * 8));
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else if (n == kUnitPx) {
+            uint32_t w[UB / 4];
+            pack(r, w);
+#pragma unroll
+            for (int k = 0; k < UB / CH; ++k) {
+                if constexpr (CH == 16)
+                    store_any(dst + k * 16, ux4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]});
+                else
+                    store_any(dst + k * 8, ux2{w[2 * k], w[2 * k + 1]});
             }
         } else {
 #pragma unroll
