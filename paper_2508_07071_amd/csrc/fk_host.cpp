@@ -232,6 +232,20 @@ bool fk::config_valid(const fk_launch_config &c)
     return t && k;
 }
 
+// Whether a run-time chain takes pixel-strided lanes: bilinear reads on large
+// launches, as the normalise kernel does (256 NV12 crops: 33.0 vs 35.5 us;
+// nearest and 1:1 NV12 reads gained nothing).  One packed channel keeps the
+// 4-pixel units: at coarsening 1 the two are level (0.2 to 0.5 GB of u8, fp16
+// and fp32 crops within 8 % either way), and above it the units run an op list
+// on up to 32 values at once where strided lanes run it on 4 (312 crops to 277
+// x 717 through 70 ops at 64 x 8 290 us, strided 490; 624 to 491 x 40 at 512 x
+// 8 130 and 266).
+static bool strided_lanes(const fk_plan *p, bool large)
+{
+    return large && p->family == FAM_RUNTIME && rd_bilinear(p->chain.read.kind) &&
+           (p->chain.write.layout == FK_PLANAR || p->chain.read.channels > 1);
+}
+
 const void *fk::plan_kernel(const fk_plan *p, const fk_launch_config &cfg, bool large)
 {
     if (p->chain.write.layout == FK_STATS) {
@@ -259,11 +273,8 @@ const void *fk::plan_kernel(const fk_plan *p, const fk_launch_config &cfg, bool 
         return kernel_muladd_loop(p->chain.read.in_dtype, p->chain.read.channels, cfg.coarsen,
                                   p->opts.strict_fp);
     default: {
-        // bilinear reads take pixel-strided lanes on large launches, as the
-        // normalise kernel does (256 NV12 crops: 33.0 vs 35.5 us; nearest and
-        // 1:1 NV12 reads gained nothing)
         int layout = p->chain.write.layout;
-        if (large && rd_bilinear(p->chain.read.kind))
+        if (strided_lanes(p, large))
             layout = layout == FK_PLANAR ? LY_PLANAR_PX : LY_PACKED_PX;
         return kernel_runtime(p->chain.read.kind, p->chain.read.in_dtype, p->chain.read.channels,
                               p->chain.write.out_dtype, layout, cfg.coarsen);

@@ -21,8 +21,9 @@ constexpr bool rd_resizes(int rk) { return rk == RD_CROP_RESIZE || rk == RD_CROP
 constexpr bool rd_bilinear(int rk) { return rk == RD_CROP_RESIZE || rk == RD_NV12_RESIZE; }
 enum : int32_t { DT_U8 = 0, DT_F16 = 1, DT_F32 = 2, DT_F64 = 3 };
 enum : int32_t { LY_PACKED = 0, LY_PLANAR = 1, LY_STATS = 2 };
-// Kernel selection only: a planar or packed write from pixel-strided lanes
-// (bilinear reads on launches of at least kStridedMinPixels output pixels).
+// Kernel selection only: a planar write, or a packed one of several channels,
+// from pixel-strided lanes (bilinear reads on launches of at least
+// kStridedMinPixels output pixels).
 enum : int32_t { LY_PLANAR_PX = 3, LY_PACKED_PX = 4 };
 
 // Normalised compute op codes.  SUB becomes ADD of the negated constant

@@ -43,8 +43,7 @@ struct RuntimeTable {
     static const void *by_layout(int ly, int k)
     {
         if constexpr (Strided) {
-            // one channel: packed and planar are the same bytes
-            if (ly == LY_PLANAR_PX || (C == 1 && ly == LY_PACKED_PX))
+            if (ly == LY_PLANAR_PX)
                 return by_coarsening<C, DO, LY_PLANAR_PX>(k);
             if constexpr (C > 1) {
                 if (ly == LY_PACKED_PX)
