@@ -292,7 +292,7 @@ bool fk::per_pixel(const fk_plan *p)
     return p->family == FAM_MULADD_LOOP && p->static_n >= kLoopPxMinPairs;
 }
 
-size_t fk::lds_bytes(const fk_plan *p, const fk_launch_config &cfg)
+size_t fk::lds_bytes(const fk_plan *p, const fk_launch_config &cfg, bool large)
 {
     if (p->family == FAM_F64)  // a pixel of doubles per thread, staged by packed writes
         return p->chain.write.layout == FK_PACKED && p->chain.read.channels > 1
@@ -300,8 +300,8 @@ size_t fk::lds_bytes(const fk_plan *p, const fk_launch_config &cfg)
                    : 0;
     if (p->family == FAM_NORMALIZE && p->opts.gather == FK_GATHER_LDS)
         return lds_gather_bytes((uint32_t)cfg.block_threads);
-    if (p->chain.write.layout != FK_PACKED || per_pixel(p))
-        return 0;
+    if (p->chain.write.layout != FK_PACKED || per_pixel(p) || strided_lanes(p, large))
+        return 0;  // stored from the lanes
     const int ub = kUnitPx * p->chain.read.channels * dtype_size(p->chain.write.out_dtype);
     if (ub == 16 || ub == 8)
         return 0;
@@ -627,7 +627,7 @@ fk_status fk::launch_args(const fk_plan *p, const fk_launch_config &cfg, KArgs &
         return set_error(FK_ERR_UNSUPPORTED, "no kernel for coarsening %d", cfg.coarsen);
     const bool stats = p->chain.write.layout == FK_STATS;
     void *args[] = {&a};
-    hipError_t e = launch_one(fn, dim3(grid), dim3(cfg.block_threads), args, lds_bytes(p, cfg),
+    hipError_t e = launch_one(fn, dim3(grid), dim3(cfg.block_threads), args, lds_bytes(p, cfg, large),
                               stream, ev0, stats ? nullptr : ev1);
     if (e == hipSuccess && stats) {
         const void *fin = kernel_stats_final(p->chain.read.channels);

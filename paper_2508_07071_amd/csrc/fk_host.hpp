@@ -57,7 +57,7 @@ bool runs_op_list(const fk_plan *p);
 // The plan's kernel for a launch configuration; `large`: the launch covers
 // at least kStridedMinPixels output pixels.
 const void *plan_kernel(const fk_plan *p, const fk_launch_config &cfg, bool large = true);
-size_t lds_bytes(const fk_plan *p, const fk_launch_config &cfg);
+size_t lds_bytes(const fk_plan *p, const fk_launch_config &cfg, bool large);
 uint32_t build_items(const fk_plan *p, const fk_item *items, int32_t n, const fk_launch_config &cfg,
                      ItemRec *recs, uint32_t *tb, int32_t batch_n = 0);
 uint32_t build_table(const fk_plan *p, const fk_item *items, int32_t n, const fk_launch_config &cfg,
