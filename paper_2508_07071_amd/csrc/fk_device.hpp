@@ -120,7 +120,22 @@ __device__ __forceinline__ void store_nt(gdst_t p, V v)
     __builtin_nontemporal_store(v, (FK_GLOBAL V *)p);
 }
 
-// The same for 8 or 16 bytes at element alignment.
+// Whether every plane of a planar output starts on a 128-byte line.  A wave's
+// run of a plane is then whole lines.  Where it is not, the lines at a run's
+// ends are shared with the neighbouring waves: written by nontemporal stores
+// they leave in parts, and more so the more waves are in flight, so kernels
+// that store several planes pixel by pixel use ordinary stores there, which
+// the L2 merges: 16 u8 crops to 1920 x 1080 x 4, one element off a line, 200 us
+// nontemporal and 130 ordinary (168 when fewer waves fitted); 400 of about 304
+// x 154 x 4 110 and 70; 16 to 1920 x 1080 x 3 136 and 94.  (700 crops to 64 x
+// 128 x 3 28 and 30.)  The second form costs four planes on lines 3 to 5 % (64
+// crops to 640 x 640 x 4 87 and 91 us).
+__device__ __forceinline__ bool planes_on_lines(uint64_t dst, int64_t plane_bytes)
+{
+    return ((dst | (uint64_t)plane_bytes) & 127) == 0;
+}
+
+// A nontemporal store of 8 or 16 bytes at element alignment.
 template <typename V>
 __device__ __forceinline__ void store_any(gdst_t p, V v)
 {
@@ -1762,8 +1777,9 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 // pixels); the per-pixel planar stores of consecutive lanes are
 // consecutive.
 // Store pixel p's C channels to its planar output position: a 32-bit offset
-// from each plane's (uniform) base.
-template <int DO, int C>
+// from each plane's (uniform) base.  Lines: the planes start on cache lines
+// (planes_on_lines).
+template <int DO, int C, bool Lines>
 __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint32_t p, const float (&v)[C])
 {
     constexpr int ES = DSize<DO>::v;
@@ -1773,7 +1789,11 @@ __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint3
         // uniform: in scalar registers, apart from the lane's offset
         base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
                (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-        store_elem<DO>((gdst_t)base + (uint64_t)(p * ES), v[c]);  // p < 2^28
+        gdst_t q = (gdst_t)base + (uint64_t)(p * ES);  // p < 2^28
+        if constexpr (Lines)
+            store_elem<DO>(q, v[c]);
+        else
+            *(FK_GLOBAL float *)q = v[c];
     }
 }
 
@@ -1830,13 +1850,23 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
     Compute::template apply<1, C>(a, v);
 
     const int64_t plane = (int64_t)it.ow * it.oh;
+    if constexpr (!Packed && DO == DT_F32 && C > 1) {
+        if (!planes_on_lines(it.dst, plane * 4)) {
+#pragma unroll
+            for (int i = 0; i < kUnitPx; ++i)
+                if (p[i] != kNoPixel)
+                    store_planar_px<DO, C, false>((gdst_t)it.dst, plane, p[i], v[0][i]);
+            __builtin_amdgcn_sched_barrier(0);  // keeps the two forms' stores from being merged into one
+            return;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < kUnitPx; ++i)
         if (p[i] != kNoPixel) {
             if constexpr (Packed)
                 store_packed_px<DO, C>((gdst_t)it.dst, p[i], v[0][i]);
             else
-                store_planar_px<DO, C>((gdst_t)it.dst, plane, p[i], v[0][i]);
+                store_planar_px<DO, C, true>((gdst_t)it.dst, plane, p[i], v[0][i]);
         }
 }
 

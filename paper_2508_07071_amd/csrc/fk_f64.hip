@@ -147,6 +147,24 @@ __global__ __launch_bounds__(kMaxBlock) void k_f64(const KArgs a)
                 }
             }
             RuntimeCompute::template apply<1, C>(a, v);
+            // ordinary stores for planes off a line (see planes_on_lines): 400
+            // u8 frames of 493 x 35 x 3 58 us nontemporal and 35 ordinary, one
+            // of 3840 x 2160 x 3 62 and 36.  Frames of fp64 read as much as
+            // they write and are level or slower with them (3840 x 2160 x 3
+            // 64 and 76).
+            if (Planar && C > 1 && DI != DT_F64 && !planes_on_lines(it.dst, (int64_t)npx * 8)) {
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    const uint32_t p = pbase + (uint32_t)((q0 + i) * T + tid);
+                    if (p < npx) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c)
+                            dst[(int64_t)c * npx + p] = v[0][i][c];
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);  // keeps the two forms' stores apart
+                continue;
+            }
 #pragma unroll
             for (int i = 0; i < P; ++i) {
                 const uint32_t p = pbase + (uint32_t)((q0 + i) * T + tid);
