@@ -15,6 +15,20 @@ static_assert(kMlpIn == 32 && kMlpOut <= 32, "the fused passes' input and output
 // wave's registers; wider ones take one product per launch.
 constexpr int kMlpMaxH = 128;
 
+// Whether the forward pass of `rows` rows takes the fused kernel (H <=
+// kMlpMaxH).  It costs about the same whatever H below 128, a block of 8 waves
+// for 16 rows, so on many rows of a narrow network one product a launch is the
+// faster form; the two give the same bits.  Fused and by layers, in us:
+// 65,536 rows of H = 16 39 and 36, 32 48 and 53; 262,144 of H = 48 199 and 203,
+// 64 233 and 251, 128 476 and 720; 16,384 of H = 8 26 and 20, 24 29 and 28, 60
+// 39 and 46, and 32,768 of H = 24 55 and 34, 60 75 and 58, 120 170 and 135
+// (widths that are no multiple of 16 load their weights value by value).  The
+// products' grids count blocks of 64 rows in y, at most 65,535 of them.
+constexpr bool mlp_forward_fused(int H, int rows)
+{
+    return (H % 16 == 0 ? H >= 64 || rows <= 2048 * H : rows <= 12288) || rows > 64 * 65535;
+}
+
 // Parameters (or gradients) of the layers in -> H -> H -> H -> out, weights
 // row-major [outputs][inputs].
 struct MlpNet {

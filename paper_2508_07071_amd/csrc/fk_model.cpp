@@ -206,7 +206,7 @@ MlpNet net_of(const fk_model *m)
 hipError_t forward_p(const fk_model *m, const float *x, float *const hid[kLayers - 1], float *y,
                      int rows, hipStream_t st)
 {
-    if (m->H <= kMlpMaxH)
+    if (m->H <= kMlpMaxH && mlp_forward_fused(m->H, rows))
         return mlp_forward(net_of(m), x, hid, y, rows, st);
     hipError_t e = hipSuccess;
     const float *in = x;
