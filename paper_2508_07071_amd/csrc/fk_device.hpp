@@ -1620,9 +1620,11 @@ constexpr int unit_group()
 
 // A group's units into registers.  Reads whose units can all be loaded (those
 // past the item as its first unit) take no branch per unit, so that the loads
-// of the whole group are in flight together: gathering reads always, plain
-// reads in waves without a partial unit.  (With a branch, and a wait, per
-// unit the 256-op chain over a 4K frame, 4 units a lane, took 94 us.)
+// of the whole group are in flight together: plain reads in waves without a
+// partial unit, gathering reads for every unit that some lane of the wave
+// holds.  (Plain reads with a branch, and a wait, per unit: 9 fp16 frames of
+// 1501 x 1103 x 3 through 37 ops 68 us, 63 so; the 256-op chain over a 4K frame,
+// bound by its arithmetic, is level at 93.)
 template <class Read, int G, int C>
 __device__ __forceinline__ void load_group(const ItemRec &it, const int (&oy)[G], const int (&ox0)[G],
                                            const int (&nv)[G], bool ragged, float (&v)[G][kUnitPx][C])

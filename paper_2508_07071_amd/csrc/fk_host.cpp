@@ -207,7 +207,8 @@ static const fk_launch_config kDefaultConfig = {256, 1};
 // op list of more than 32 records takes coarsening 2 after a plain read
 // and stays at 1 after the other reads: over the 22,000 labelled random
 // chains, those lists reach 0.85 (plain) and 0.92 (crop+resize) of their
-// autotuned best that way, against 0.78 and 0.63 at coarsening 4.  The
+// autotuned best that way, against 0.78 and 0.63 at coarsening 4 (labels of
+// the op list's earlier kernels, one branch per record).  The
 // compile-time loop chain loads its two constants once, so it keeps
 // coarsening 1 and with it the most waves for its arithmetic.  The stats
 // write takes coarsening 8: its plain-read tiles issue all K loads first

@@ -215,15 +215,16 @@ __global__ void k_mean(const float *__restrict__ x, int n, float *__restrict__ o
 // The whole network over a block's rows in one launch, on the fp32 matrix
 // instruction (v_mfma_f32_16x16x4: lane l holds A[l % 16][l / 16],
 // B[l / 16][l % 16] and D[4 (l / 16) + r][l % 16], r < 4; it adds its four
-// products in order, so a K loop gives k_gemm's bits).
+// products in order, so the forward pass has k_gemm's bits).
 //
 // Bound by latency at a training batch: 512 rows are 0.12 GFLOP and 0.5 MB.
 // One launch per product, four dW products of 4 to 16 blocks that walked
 // all rows (93 us each) and four column sums of one thread per column (96 us
-// each) took 885 us for forward, loss and backward.  Here a pass is one
+// each) took 880 us for forward, loss and backward.  Here a pass is one
 // launch (two for the backward), 16 rows a block, all weights fetched at
 // once, and the reductions over rows split over the waves of a block:
-// 40 us (12.7 forward, 4.3 loss, 6.2 deltas, 18 gradients).
+// 40 us (12.7 forward, 4.3 loss, 6.2 deltas, 18 gradients; the last has 152
+// blocks, of which the 8 of layer 0 walk all rows through two products).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRows = 16;         // rows of a block: one tile
 constexpr int kWaves = 8;         // one 16-column tile of a 128-wide layer each
