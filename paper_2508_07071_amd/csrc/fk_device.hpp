@@ -1339,8 +1339,12 @@ struct WritePlanar {
 // 363 x 3 into packed fp16 took 104 us with element stores); other waves store
 // their whole units from the lanes in 16-byte pieces (rows with a partial unit
 // in every wave: 700 fp32 frames of about 86 x 415 x 3 into packed fp32 445 us
-// with element stores, 243 so), and the partial ones value by value.
-template <int DT, int C>
+// with element stores, 243 so), and the partial ones value by value.  Pieces:
+// false for the compile-time chains, whose other waves store every unit value
+// by value: the pieces' register tuples took their tiles of 4 and 8 units from
+// 73 to 106 registers (2 frames of 24 x 100 x 3 through 16 ops at 1024 x 4 4.7
+// and 7.2 us), and their waves in flight were always as many.
+template <int DT, int C, bool Pieces = true>
 struct WritePacked {
     static constexpr int layout = LY_PACKED;
     static constexpr int dtype = DT;
@@ -1405,7 +1409,7 @@ struct WritePacked {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else if (n == kUnitPx) {
+        } else if (n == kUnitPx && (Pieces || all_whole)) {
             uint32_t w[UB / 4];
             pack(r, w);
 #pragma unroll
