@@ -471,8 +471,7 @@ struct ReadCropResize {
         return !window_ok(it) ? 0 : (it.flags & IF_SMALL_FRAME) ? 2 : 1;
     }
     __device__ __forceinline__ static void load_pxs(const ItemRec &it, int prep, const int (&oy)[kUnitPx],
-                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C],
-                                                    int n = kUnitPx)
+                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C], int n)
     {
         if constexpr (DT == DT_U8) {
             if (prep == 2) {
@@ -792,8 +791,7 @@ struct ReadNV12Resize {
         return !window_ok(it) ? 0 : small ? 2 : 1;
     }
     __device__ __forceinline__ static void load_pxs(const ItemRec &it, int prep, const int (&oy)[kUnitPx],
-                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C],
-                                                    int n = kUnitPx)
+                                                    const int (&ox)[kUnitPx], float (&r)[kUnitPx][C], int n)
     {
         if (prep == 2)
             pixels<2>(it, oy, ox, r, n);
@@ -1906,12 +1904,14 @@ __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint3
             break;
         float v[1][kUnitPx][C];
         uint32_t p[kUnitPx];
-        int oy[kUnitPx], ox[kUnitPx];
+        int oy[kUnitPx], ox[kUnitPx], n = 0;
 #pragma unroll
         for (int i = 0; i < kUnitPx; ++i) {
             // lanes past the item read its first pixel and store nothing: no
             // branch per pixel, so that the gathers are in flight together
+            // (byte-by-byte reads leave them out)
             const bool in = at < npx;
+            n += in ? 1 : 0;
             p[i] = in ? at : kNoPixel;
             oy[i] = in ? (int)row : 0;
             ox[i] = in ? (int)col : 0;
@@ -1923,7 +1923,7 @@ __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint3
                 ++row;
             }
         }
-        Read::load_pxs(it, prep, oy, ox, v[0]);
+        Read::load_pxs(it, prep, oy, ox, v[0], n);
         chain_store_px<Compute, DO, C, Packed>(a, it, v, p);
     }
 }
