@@ -618,10 +618,13 @@ static hipError_t launch_one(const void *fn, dim3 grid, dim3 block, void **args,
 }
 
 fk_status fk::launch_args(const fk_plan *p, const fk_launch_config &cfg, KArgs &a, uint32_t grid,
-                          int32_t n_items, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
+                          int32_t n_items, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, uint64_t run_tiles)
 {
-    // output pixels the launch covers: grid blocks of T * K units of 4 pixels
-    const uint64_t px = (uint64_t)grid * (uint64_t)cfg.block_threads * (uint64_t)cfg.coarsen * kUnitPx;
+    // Output pixels the run covers: tiles of T * K units of 4 pixels.  A run of
+    // several launches is taken as a whole (run_tiles), as its one launch from
+    // a table would be: 312 crops of 7 frames to 48 x 72, 156 a launch, 18.3 us
+    // by each launch and 13.0 by the run; 800 of one frame 21.0 and 18.5.
+    const uint64_t px = std::max<uint64_t>(grid, run_tiles) * (uint64_t)cfg.block_threads * (uint64_t)cfg.coarsen * kUnitPx;
     const bool large = px >= (p->chain.read.in_dtype == FK_U8 ? kStridedMinPixels : kStridedMinPixelsWide);
     const void *fn = plan_kernel(p, cfg, large);
     if (!fn)
@@ -679,10 +682,10 @@ int fk::compact_batch(const fk_plan *p, const fk_item *items, int32_t n)
 // One compact kernel-argument launch of n items (1 <= n <= the form's
 // capacity) that share the template of items[0]; item b's output is
 // items[0].dst + b * stride.  batch_n is the batch size the per-item tiling
-// assumes.
+// assumes, run_n the items of the run where that has more launches.
 static fk_status launch_compact(const fk_plan *p, int form, const fk_item *items, int32_t n, intptr_t stride,
                                 int32_t batch_n, const fk_launch_config &cfg, hipStream_t stream,
-                                hipEvent_t ev0, hipEvent_t ev1)
+                                hipEvent_t ev0, hipEvent_t ev1, int32_t run_n = 0)
 {
     KArgs a = make_args(p, nullptr);
     a.hdr = nullptr;
@@ -719,7 +722,7 @@ static fk_status launch_compact(const fk_plan *p, int form, const fk_item *items
             ((Roi16 *)(a.inl + 64))[b] = roi;
     }
     const uint32_t grid = std::min<uint32_t>(a.inl_total_tiles, 1u << 20);
-    return launch_args(p, cfg, a, grid, n, stream, ev0, ev1);
+    return launch_args(p, cfg, a, grid, n, stream, ev0, ev1, (uint64_t)a.inl_tiles_per_item * (uint64_t)run_n);
 }
 
 static_assert(sizeof(RunHeader) % 16 == 0 && sizeof(ItemRec) % 16 == 0,
@@ -813,7 +816,7 @@ fk_status fk::run_fused(fk_plan *p, const fk_item *items, int32_t n, const fk_la
             for (int32_t b0 = 0; b0 < n; b0 += cap) {
                 const int32_t m = std::min(n - b0, cap);
                 fk_status s = launch_compact(p, form, items + b0, m, stride, m, cfg, stream,
-                                             b0 == 0 ? ev0 : nullptr, b0 + m == n ? ev1 : nullptr);
+                                             b0 == 0 ? ev0 : nullptr, b0 + m == n ? ev1 : nullptr, n);
                 if (s)
                     return s;
             }

@@ -65,7 +65,8 @@ uint32_t build_table(const fk_plan *p, const fk_item *items, int32_t n, const fk
 KArgs make_args(const fk_plan *p, void *d_table);
 uint32_t persistent_grid(const fk_plan *p, const fk_launch_config &cfg);
 fk_status launch_args(const fk_plan *p, const fk_launch_config &cfg, KArgs &a, uint32_t grid, int32_t n_items,
-                      hipStream_t stream, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                      hipStream_t stream, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                      uint64_t run_tiles = 0);
 fk_status launch(const fk_plan *p, const fk_launch_config &cfg, void *d_table, uint32_t grid,
                  int32_t n_items, hipStream_t stream, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);

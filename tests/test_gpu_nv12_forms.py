@@ -1,4 +1,4 @@
-"""NV12 batches whose items travel in the kernel arguments, on frames whose
+"""Batches whose items travel in the kernel arguments, NV12 above all, on frames whose
 base and pitch are multiples of 4: a 1:1 read then takes whole dwords at the
 columns that are multiples of 4 and bytes at the others, item by item, also
 where the last launch of a split batch holds one item (625 and 1249 corners
@@ -34,7 +34,8 @@ def batch(kind, n, frames, last_x):
 def check(ch, items, frs, dframes):
     refs = oracle.run_chain(ch, frs, items)
     n = len(items)
-    out = torch.full((n,) + tuple(fk.out_shape(ch, items[0])), float("nan"), dtype=torch.float32, device="cuda")
+    dt = fk.TORCH_DTYPE[ch["write"]["dtype"]]
+    out = torch.full((n,) + tuple(fk.out_shape(ch, items[0])), float("nan"), dtype=dt, device="cuda")
     with H.Plan(ch, n, strict=True) as p:
         p.run(dframes, items, outs=[out[i] for i in range(n)])
     got = out.cpu().numpy()
@@ -63,3 +64,20 @@ def test_frames_of_mixed_alignment(n, odd_frame, offset):
     buf[offset:offset + size] = dframes[odd_frame].reshape(-1)
     dframes[odd_frame] = buf[offset:offset + size].view(frs[odd_frame].shape)
     check(ch, items, frs, dframes)
+
+
+@pytest.mark.parametrize("kind", ["crop_resize", "nv12_resize"])
+@pytest.mark.parametrize("dtype,layout", [("f32", "planar"), ("f16", "packed")])
+@pytest.mark.parametrize("n,frames", [(157, 5), (313, 1)])
+def test_split_run_in_strided_lanes(kind, dtype, layout, n, frames):
+    """A run of 2^20 pixels and more takes pixel-strided lanes in each of its
+    launches, the last one of a single item (NV12 and BGR)."""
+    ch, frs, items = batch("nv12_resize", n, frames, 3)
+    if kind == "crop_resize":
+        g = datagen.rng(n)
+        frs = [datagen.frame(g, FH, FW, 3, "u8") for _ in range(frames)]
+    ch["read"]["kind"], ch["write"] = kind, {"dtype": dtype, "layout": layout}
+    for it in items:
+        it.update(out_w=97, out_h=71)
+    assert n * 97 * 71 >= 1 << 20
+    check(ch, items, frs, H.to_dev(frs))
