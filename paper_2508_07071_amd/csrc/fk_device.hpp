@@ -123,16 +123,29 @@ __device__ __forceinline__ void store_nt(gdst_t p, V v)
 // Whether every plane of a planar output starts on a 128-byte line.  A wave's
 // run of a plane is then whole lines.  Where it is not, the lines at a run's
 // ends are shared with the neighbouring waves: written by nontemporal stores
-// they leave in parts, and more so the more waves are in flight, so kernels
-// that store several planes pixel by pixel use ordinary stores there, which
-// the L2 merges: 16 u8 crops to 1920 x 1080 x 4, one element off a line, 200 us
-// nontemporal and 130 ordinary (168 when fewer waves fitted); 400 of about 304
-// x 154 x 4 110 and 70; 16 to 1920 x 1080 x 3 136 and 94.  (700 crops to 64 x
-// 128 x 3 28 and 30.)  The second form costs four planes on lines 3 to 5 % (64
-// crops to 640 x 640 x 4 87 and 91 us).
+// they leave in parts, and more so the more waves are in flight; ordinary
+// stores are merged in the L2.
 __device__ __forceinline__ bool planes_on_lines(uint64_t dst, int64_t plane_bytes)
 {
     return ((dst | (uint64_t)plane_bytes) & 127) == 0;
+}
+
+// Whether a gather in strided lanes stores its planes by ordinary stores: only
+// off a line, as four planes on lines pay 3 to 5 % for the second form (64
+// crops to 640 x 640 x 4 87 and 91 us); off one (us, nontemporal / ordinary) 4
+// crops to 1919 x 1079 x 3 30 / 25 and 338 to 305 x 155 x 4 78 / 66.  Ordinary
+// stores put the frames out of the caches, though, when a launch writes more
+// than the last level's 256 MiB: 705 crops of 60 frames to 305 x 155 x 3 (400
+// MB) 130 / 170.  Planes of 2 MiB and more are merged there all the same: 36
+// crops of one frame to 1920 x 1080 x 3 295 / 214, of 60 frames 281 / 308.
+// Byte-by-byte reads of three channels, which wait for each pixel, win by
+// merging only when both hold: 8 crops to 1919 x 1079 x 3 (200 MB) 62 / 52, 16
+// of 20 frames (400 MB) 133 / 200, 42 to 305 x 155 x 3 12 / 14.
+__device__ __forceinline__ bool merge_planes(uint64_t dst, int64_t plane_bytes, uint64_t launch_bytes,
+                                             bool bytewise)
+{
+    const bool big = plane_bytes >= (2 << 20), fits = launch_bytes <= (256u << 20);
+    return !planes_on_lines(dst, plane_bytes) && (bytewise ? big && fits : big || fits);
 }
 
 // A nontemporal store of 8 or 16 bytes at element alignment.
@@ -1781,9 +1794,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_transform(const KArgs a)
 // pixels); the per-pixel planar stores of consecutive lanes are
 // consecutive.
 // Store pixel p's C channels to its planar output position: a 32-bit offset
-// from each plane's (uniform) base.  Lines: the planes start on cache lines
-// (planes_on_lines).
-template <int DO, int C, bool Lines>
+// from each plane's (uniform) base.  Merge: ordinary stores (merge_planes).
+template <int DO, int C, bool Merge>
 __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint32_t p, const float (&v)[C])
 {
     constexpr int ES = DSize<DO>::v;
@@ -1794,7 +1806,7 @@ __device__ __forceinline__ void store_planar_px(gdst_t dst, int64_t plane, uint3
         base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
                (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         gdst_t q = (gdst_t)base + (uint64_t)(p * ES);  // p < 2^28
-        if constexpr (Lines)
+        if constexpr (!Merge)
             store_elem<DO>(q, v[c]);
         else
             *(FK_GLOBAL float *)q = v[c];
@@ -1837,7 +1849,7 @@ constexpr uint32_t kNoPixel = 0xffffffffu;
 
 template <class Compute, int DO, int C, bool Packed = false>
 __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it, float (&v)[1][kUnitPx][C],
-                                               const uint32_t (&p)[kUnitPx])
+                                               const uint32_t (&p)[kUnitPx], bool merge = false)
 {
     if constexpr (C >= 3) {
         // run-time tier: the chain's net channel swap, applied at the read
@@ -1855,11 +1867,11 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
 
     const int64_t plane = (int64_t)it.ow * it.oh;
     if constexpr (!Packed && DO == DT_F32 && C > 1) {
-        if (!planes_on_lines(it.dst, plane * 4)) {
+        if (merge) {
 #pragma unroll
             for (int i = 0; i < kUnitPx; ++i)
                 if (p[i] != kNoPixel)
-                    store_planar_px<DO, C, false>((gdst_t)it.dst, plane, p[i], v[0][i]);
+                    store_planar_px<DO, C, true>((gdst_t)it.dst, plane, p[i], v[0][i]);
             __builtin_amdgcn_sched_barrier(0);  // keeps the two forms' stores from being merged into one
             return;
         }
@@ -1870,7 +1882,7 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
             if constexpr (Packed)
                 store_packed_px<DO, C>((gdst_t)it.dst, p[i], v[0][i]);
             else
-                store_planar_px<DO, C, true>((gdst_t)it.dst, plane, p[i], v[0][i]);
+                store_planar_px<DO, C, false>((gdst_t)it.dst, plane, p[i], v[0][i]);
         }
 }
 
@@ -1885,13 +1897,17 @@ __device__ __forceinline__ void chain_store_px(const KArgs &a, const ItemRec &it
 // do not depend on the clamp, and the division by reciprocal it takes 94 us;
 // 256 NV12 crops 15.5 -> 12.8 us.
 template <class Read, class Compute, int DO, int C, int K, bool Packed = false>
-__device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint32_t ubase, int T, int tid)
+__device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint32_t ubase, int T, int tid,
+                                        uint32_t total)
 {
     const uint32_t ow = (uint32_t)it.ow;
     const uint32_t npx = ow * (uint32_t)it.oh;  // <= 2^28
     const RowDiv rowdiv(ow);
     const uint32_t step_rows = rowdiv((uint32_t)T), step_cols = (uint32_t)T - __umul24(step_rows, ow);
     const auto prep = Read::px_prep(it);
+    // total: the launch's tiles
+    const bool merge = merge_planes(it.dst, (int64_t)npx * 4, (uint64_t)total * ((uint32_t)(T * K) * kUnitPx) * (C * 4),
+                                    C == 3 && Read::elem_size == 1 && prep == 0);
     uint32_t at = ubase * kUnitPx + (uint32_t)tid;
     uint32_t row = rowdiv(at), col = at - __umul24(row, ow);
 
@@ -1924,7 +1940,7 @@ __device__ __forceinline__ void px_tile(const KArgs &a, const ItemRec &it, uint3
             }
         }
         Read::load_pxs(it, prep, oy, ox, v[0], n);
-        chain_store_px<Compute, DO, C, Packed>(a, it, v, p);
+        chain_store_px<Compute, DO, C, Packed>(a, it, v, p, merge);
     }
 }
 
@@ -1947,7 +1963,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_px(const KArgs a)
         ItemRec it;
         uint32_t ubase;
         tile_item<Read, C>(a, ka, compact, tb, items, n_items, tile, total, tile_units, it, ubase);
-        px_tile<Read, Compute, DO, C, K, Packed>(a, it, ubase, T, tid);
+        px_tile<Read, Compute, DO, C, K, Packed>(a, it, ubase, T, tid, total);
     }
 }
 
@@ -2030,12 +2046,14 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_lds(const KArgs a)
         const uint32_t npx = (uint32_t)it.ow * (uint32_t)it.oh;
         // uniform over the block: every lane takes the same branch
         if (npx >= (1u << 28) || !lds_gather_plan<C>(it, lds_bytes, g)) {
-            px_tile<Read, Compute, DO, C, K>(a, it, ubase, T, tid);
+            px_tile<Read, Compute, DO, C, K>(a, it, ubase, T, tid, total);
             continue;
         }
         const uint32_t ow = (uint32_t)it.ow;
         const uint32_t pbase = ubase * kUnitPx;
         const uint32_t pend = min(pbase + (uint32_t)kUnitPx * tile_units, npx);
+        const bool merge =
+            merge_planes(it.dst, (int64_t)npx * 4, (uint64_t)total * (tile_units * kUnitPx) * (C * 4), false);
         const RowDiv rowdiv(ow);
         const RowDiv chunkdiv(g.n16);
         const uint32_t r_last = rowdiv(pend - 1);
@@ -2081,7 +2099,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_resize_lds(const KArgs a)
                             v[0][i][c] = 0.0f;
                     }
                 }
-                chain_store_px<Compute, DO, C>(a, it, v, px);
+                chain_store_px<Compute, DO, C>(a, it, v, px, merge);
             }
         }
     }
