@@ -1350,12 +1350,12 @@ struct WritePlanar {
 // 363 x 3 into packed fp16 took 104 us with element stores); other waves store
 // their whole units from the lanes in 16-byte pieces (rows with a partial unit
 // in every wave: 700 fp32 frames of about 86 x 415 x 3 into packed fp32 445 us
-// with element stores, 243 so), and the partial ones value by value.  Pieces:
-// false for the compile-time chains, whose other waves store every unit value
-// by value: the pieces' register tuples took their tiles of 4 and 8 units from
-// 73 to 106 registers (2 frames of 24 x 100 x 3 through 16 ops at 1024 x 4 4.7
-// and 7.2 us), and their waves in flight were always as many.
-template <int DT, int C, bool Pieces = true>
+// with element stores, 243 so), and the partial ones value by value.  Piece: 8
+// for the compile-time chains, in whose tiles of 4 and 8 units the tuples of 4
+// registers took 73 registers to 106 (2 frames of 24 x 100 x 3 through 16 ops
+// at 1024 x 4: 3.9 us with element stores, 5.3 in pieces of 16 bytes, 4.6 of 8;
+// 700 frames of 57 x 626 x 3 418, 203 and 210).
+template <int DT, int C, int Piece = 16>
 struct WritePacked {
     static constexpr int layout = LY_PACKED;
     static constexpr int dtype = DT;
@@ -1420,12 +1420,13 @@ struct WritePacked {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else if (n == kUnitPx && (Pieces || all_whole)) {
+        } else if (n == kUnitPx) {
+            constexpr int PB = CH < Piece ? CH : Piece;
             uint32_t w[UB / 4];
             pack(r, w);
 #pragma unroll
-            for (int k = 0; k < UB / CH; ++k) {
-                if constexpr (CH == 16)
+            for (int k = 0; k < UB / PB; ++k) {
+                if constexpr (PB == 16)
                     store_any(dst + k * 16, ux4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]});
                 else
                     store_any(dst + k * 8, ux2{w[2 * k], w[2 * k + 1]});

@@ -111,7 +111,7 @@ template <int N, bool Strict, int K>
 static const void *muladd_ptr()
 {
     return (const void *)&k_transform<ReadPlain<DT_U8, 3>, StaticCompute<MulAddChain<N, Strict>>,
-                                      WritePacked<DT_F32, 3, false>, 3, K>;
+                                      WritePacked<DT_F32, 3, 8>, 3, K>;
 }
 
 template <int N>
@@ -143,7 +143,7 @@ template <int DI, int C, bool Strict, int K>
 static const void *loop_ptr()
 {
     return (const void *)&k_transform<ReadPlain<DI, C>, LoopMulAddCompute<Strict>,
-                                      WritePacked<DT_F32, C, false>, C, K>;
+                                      WritePacked<DT_F32, C, C == 1 ? 16 : 8>, C, K>;
 }
 
 template <int DI, int C>
